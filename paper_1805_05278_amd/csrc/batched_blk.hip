@@ -46,6 +46,7 @@
 
 #include "batched.h"
 #include "common.h"
+#include "lanes.h"
 
 namespace miqr {
 namespace {
@@ -119,178 +120,6 @@ __device__ __forceinline__ s4 pack_bf16(f4 v) {
 // 16x16x16 BF16 MFMA: a = A[l % 16][4 (l / 16) + j], b = B[4 (l / 16) + j][l % 16].
 __device__ __forceinline__ f4 mma_bf16(f4 a, f4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pack_bf16(a), pack_bf16(b), c, 0, 0, 0);
-}
-
-__device__ __forceinline__ unsigned lo32(double v) {
-  return (unsigned)(unsigned long long)__double_as_longlong(v);
-}
-__device__ __forceinline__ unsigned hi32(double v) {
-  return (unsigned)((unsigned long long)__double_as_longlong(v) >> 32);
-}
-__device__ __forceinline__ double join(unsigned lo, unsigned hi) {
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// Sum over the four lanes cl, cl + 16, cl + 32, cl + 48: rows paired by
-// v_permlane16_swap, then halves by v_permlane32_swap; each swap leaves one
-// copy holding the lower partner in both places and the other the upper, so
-// every lane forms the same sums in the same order.
-__device__ __forceinline__ double rows_sum(double v) {
-  {
-    const auto l = __builtin_amdgcn_permlane16_swap(lo32(v), lo32(v), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(hi32(v), hi32(v), false, false);
-    v = join(l[0], h[0]) + join(l[1], h[1]);
-  }
-  {
-    const auto l = __builtin_amdgcn_permlane32_swap(lo32(v), lo32(v), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(hi32(v), hi32(v), false, false);
-    v = join(l[0], h[0]) + join(l[1], h[1]);
-  }
-  return v;
-}
-
-__device__ __forceinline__ double readlane(double v, int lane) {
-  return join((unsigned)__builtin_amdgcn_readlane((int)lo32(v), lane),
-              (unsigned)__builtin_amdgcn_readlane((int)hi32(v), lane));
-}
-
-// The pivot broadcast fused into the FMAs: v_fmac_{f64,f32}_dpp with
-// row_newbcast:J reads its first source from lane J of the lane's row.  One
-// s_nop 1 at the head of each block gives the two wait states a DPP read
-// needs after a VALU write of its source (the compiler does not look inside
-// the asm); within a block no instruction DPP-reads a register written by
-// the one before it.  xs[4 t + r] is register r of row tile t.
-//   d0 += sum_t (x_J[t][0] x[t][0] + x_J[t][2] x[t][2]), d1 likewise for
-//   registers 1 and 3 (two chains for latency).
-template <int J>
-__device__ __forceinline__ void dots_bcast(const double (&xs)[16], double& d0, double& d1) {
-  asm("s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, %2, %2 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %3, %3 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %0, %4, %4 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %5, %5 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %0, %6, %6 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %7, %7 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %0, %8, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %9, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %0, %10, %10 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %11, %11 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %0, %12, %12 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %13, %13 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %0, %14, %14 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %15, %15 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %0, %16, %16 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %17, %17 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(d0), "+v"(d1)
-      : "v"(xs[0]), "v"(xs[1]), "v"(xs[2]), "v"(xs[3]), "v"(xs[4]), "v"(xs[5]), "v"(xs[6]), "v"(xs[7]), "v"(xs[8]), "v"(xs[9]), "v"(xs[10]), "v"(xs[11]), "v"(xs[12]), "v"(xs[13]), "v"(xs[14]), "v"(xs[15]), "n"(J));
-}
-template <int J>
-__device__ __forceinline__ void dots_bcast(const float (&xs)[16], float& d0, float& d1) {
-  asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, %2, %2 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %3, %3 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %0, %4, %4 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %5, %5 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %0, %6, %6 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %7, %7 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %0, %8, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %9, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %0, %10, %10 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %11, %11 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %0, %12, %12 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %13, %13 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %0, %14, %14 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %15, %15 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %0, %16, %16 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %17, %17 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(d0), "+v"(d1)
-      : "v"(xs[0]), "v"(xs[1]), "v"(xs[2]), "v"(xs[3]), "v"(xs[4]), "v"(xs[5]), "v"(xs[6]), "v"(xs[7]), "v"(xs[8]), "v"(xs[9]), "v"(xs[10]), "v"(xs[11]), "v"(xs[12]), "v"(xs[13]), "v"(xs[14]), "v"(xs[15]), "n"(J));
-}
-//   x[t][r] += x_J[t][r] nf (lane J's own entries are unchanged when its nf
-//   is zero).
-template <int J>
-__device__ __forceinline__ void update_bcast(double (&xs)[16], double nf) {
-  asm("s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, %0, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %1, %1, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %2, %2, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %3, %3, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %4, %4, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %5, %5, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %6, %6, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %7, %7, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %8, %8, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %9, %9, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %10, %10, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %11, %11, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %12, %12, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %13, %13, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %14, %14, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f64_dpp %15, %15, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(xs[0]), "+v"(xs[1]), "+v"(xs[2]), "+v"(xs[3]), "+v"(xs[4]), "+v"(xs[5]), "+v"(xs[6]), "+v"(xs[7]), "+v"(xs[8]), "+v"(xs[9]), "+v"(xs[10]), "+v"(xs[11]), "+v"(xs[12]), "+v"(xs[13]), "+v"(xs[14]), "+v"(xs[15])
-      : "v"(nf), "n"(J));
-}
-template <int J>
-__device__ __forceinline__ void update_bcast(float (&xs)[16], float nf) {
-  asm("s_nop 1\n\t"
-      "v_fmac_f32_dpp %0, %0, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %1, %1, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %2, %2, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %3, %3, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %4, %4, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %5, %5, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %6, %6, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %7, %7, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %8, %8, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %9, %9, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %10, %10, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %11, %11, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %12, %12, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %13, %13, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %14, %14, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      "v_fmac_f32_dpp %15, %15, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(xs[0]), "+v"(xs[1]), "+v"(xs[2]), "+v"(xs[3]), "+v"(xs[4]), "+v"(xs[5]), "+v"(xs[6]), "+v"(xs[7]), "+v"(xs[8]), "+v"(xs[9]), "+v"(xs[10]), "+v"(xs[11]), "+v"(xs[12]), "+v"(xs[13]), "+v"(xs[14]), "+v"(xs[15])
-      : "v"(nf), "n"(J));
-}
-
-// Lane group QJ's value to all four groups (lanes cl, cl + 16, cl + 32,
-// cl + 48): v_permlane16_swap leaves rows (0, 0, 2, 2) in one copy and
-// (1, 1, 3, 3) in the other, v_permlane32_swap then halves (0, 1, 0, 1) and
-// (2, 3, 2, 3).
-template <int QJ>
-__device__ __forceinline__ double group_bcast(double v) {
-  unsigned lo = lo32(v), hi = hi32(v);
-  {
-    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    lo = (QJ & 1) ? l[1] : l[0];
-    hi = (QJ & 1) ? h[1] : h[0];
-  }
-  {
-    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    lo = (QJ & 2) ? l[1] : l[0];
-    hi = (QJ & 2) ? h[1] : h[0];
-  }
-  return join(lo, hi);
-}
-
-// The lane index through an empty asm: addresses, masks and row numbers made
-// from it are then computed where they are used.  Otherwise the compiler
-// hoists them out of the sweep's loops as invariants and holds dozens of
-// them in registers for the whole problem, spilling the tiles.
-// Workgroup barrier that orders LDS only: global loads in flight (a
-// prefetch) stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-__device__ __forceinline__ int lane_id() {
-  int l = threadIdx.x & 63;
-  asm volatile("" : "+v"(l));
-  return l;
 }
 
 // LDS buffers for the panels' Y and T: panel p uses buffer p mod NBUF.  With

@@ -33,19 +33,12 @@
 #include <algorithm>
 
 #include "common.h"
+#include "lanes.h"
 #include "profiler.h"
 #include "tsqr.h"
 #include "plan.h"
 
 namespace miqr {
-
-// A copy of v that the compiler cannot merge with other uses of v: index
-// arithmetic built on it is recomputed where it is used instead of being kept
-// live (and spilled) across the kernel.
-__device__ __forceinline__ int fresh_copy(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
 
 struct ChainQRArgs {
   double* X;       // leaf level: panel (in place); tree level: child R array
@@ -57,951 +50,525 @@ struct ChainQRArgs {
   double* R;       // per chain / node
 };
 
-// Sum over N consecutive lanes (N = 8, 16 or 32), result in every lane: quad
-// sums and half-row / row mirrors through DPP, then (N = 32) an exchange
-// between the two 16-lane rows of a 32-lane group through ds_swizzle.
-template <int N>
-__device__ __forceinline__ double group_sum(double v) {
-  v = oct_sum(v);
-  if (N == 8) return v;
-  v += dpp_mov<0x140>(v);  // row_mirror: lane i <-> 15 - i
-  if (N == 32) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    int lo = __builtin_amdgcn_ds_swizzle((int)(unsigned)(b & 0xffffffffull), 0x401F);
-    int hi = __builtin_amdgcn_ds_swizzle((int)(unsigned)(b >> 32), 0x401F);
-    v += __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) |
-                                          (unsigned long long)(unsigned)lo));
-  }
-  return v;
-}
+// ------------------------------------------------------------ block QR
+//
+// One workgroup of four waves factors a block of up to 256 x 64: its own rows
+// (a chain's first leaf block), or rows stacked under an upper triangular R
+// (later leaf blocks, tree nodes).  It is the compact-WY recursion of
+// Sec. 2.3 inside the block: 16-column sub-panels, each factored column by
+// column and applied to the columns right of it with FP64 MFMA.
+//
+// Layout.  The block stays in registers: wave w holds RT row tiles of 16 rows
+// and all four column tiles, in the MFMA accumulator layout (lane (g, cl)
+// holds register r of rows m = g + 4 r of a tile in column cl).  Every column
+// therefore lies across all four waves, one on each SIMD, and a column step
+// is short everywhere at once: 4 RT products per lane for the dot products
+// with the pivot column (broadcast inside the FMAs), a sum over the four
+// lanes of a column, one exchange of 16 x 4 partial sums through LDS (the
+// step's only barrier), the reflector in every wave alike, and 4 RT FMAs of
+// update.  The pivot lane's own dot product is its squared norm, and the dot
+// products with the columns left of the pivot are the Gram entries that T is
+// built from, so a step has one sum and one exchange.  The next sub-panel is
+// always in register slot 0 (slots rotate), so the sixteen unrolled steps
+// exist once in the code.
+//   V^T X contracts over rows in the order the registers hold them, so both
+// operands come straight from registers; only V W' needs V with rows and
+// columns exchanged, through a few LDS tiles private to the wave.
+//   Bound: the chain of 64 dependent column steps (latency), not arithmetic
+// (a 256 x 64 block is about 3 MFLOP, 10 us on one CU) or memory.  LDS is
+// under 80 KB and registers under 256, so two workgroups share a CU, and one
+// fits beside a GEMM workgroup of the look-ahead stream.
+//   Measured (MI355X; before: a 512-thread body of one pivot half-wave per
+// column, 140 KB of LDS, two lane reductions per column): tree node of five
+// 64 x 64 children 72 -> 45 us, first 256 x 64 leaf blocks 107 -> 59 us at one
+// per CU, leaf chains of 1048576 x 64 (512 chains of 8) 1081 -> 735 us.  A
+// column step takes 845 cycles, 54 k of a tree node's 105 k.
+//
+// A register's row inside its tile is pi(g, r) = 8 (r / 2) + 2 g + r % 2: a
+// lane's register pairs are adjacent rows, loaded and stored as 16 bytes, and
+// the four lanes of a column cover 64 consecutive bytes.  MFMA never sees the
+// order: it only contracts over it or maps it to itself.
 
-// Register layout of a block of H rows (H = 64, 128 or 256) in a 512-thread
-// workgroup: thread t holds 8 rows of CPT = H / 64 columns cg CPT .. cg CPT +
-// CPT - 1 (cg = t / RG, RG = H / 8).  Its rows are four pairs: slot s of lane
-// rg is row 2 rg + 2 RG (s / 2) + s % 2, so that for a fixed slot pair the RG
-// lanes of a column cover 2 RG consecutive rows: global loads and stores
-// coalesce, and the lanes' 16-byte LDS reads of the reflector are
-// consecutive.  The RG threads of a column group sit in one wave, so column
-// sums are lane reductions.  Each reflector value read from LDS is reused for
-// CPT columns.
-template <int H>
-struct Lay {
-  static constexpr int RG = H / 8;
-  static constexpr int CPT = RG / 8;
-  static __device__ __forceinline__ int row(int rg, int s) {
-    return 2 * rg + 2 * RG * (s >> 1) + (s & 1);
-  }
+constexpr int kTLD = 17;            // row stride of a 16 x 16 tile in LDS
+constexpr int kTile = 16 * kTLD;    // doubles per tile
+
+// Tile (p, c), p <= c, of an upper triangle of 16 x 16 tiles.
+__device__ __forceinline__ int tri(int p, int c) { return c * (c + 1) / 2 + p; }
+
+struct NodeLds {
+  double r[10][kTile];               // running R, upper tiles, row-major
+  double t[10][kTile];               // T, upper tiles, row-major
+  double red[4][3][kTile];           // per wave: partial W of slots 1..3, then V tiles
+  double wp[3][kTile];               // slot s: W' (right of the sub-panel) or G T_b (left of it)
+  __align__(16) double part[2][16][4];  // a column step's partial dot products
+  double prow[2][16];                // and its pivot row (first blocks)
 };
 
-// One QR step on the rows held in registers (x[u][s]: column cg CPT + u, row
-// Lay<H>::row(rg, s)).
-//   first:  plain Householder QR of the rows themselves (pivot row j);
-//   !first: the rows are stacked under the upper triangular R held in Rs.
-// On return x holds the basis (rows below the pivot for `first`, all rows
-// otherwise), Rs the new R (for !first), Gs the Gram entries v_i . v_j in its
-// strict upper triangle (Gs must be zero below the diagonal and outside nbr on
-// entry), and taus the reflector scalars; build_t then turns Gs into T.  The
-// two are separate so that a caller can store x first and build T without
-// the block's registers live.
-template <int H, bool first>
-__device__ __forceinline__ void qr_step(double (&x)[Lay<H>::CPT][8], int nbr,
-                                        double (*Rs)[kNB + 1], double (*Gs)[kNB + 1],
-                                        double (*vbuf)[H], double* taus, double* Wt) {
-  constexpr int RG = Lay<H>::RG, CPT = Lay<H>::CPT;
-  const int t = threadIdx.x, rg = t % RG, cg = t / RG;
-  // The reflector sits in vb in row order: a lane's pair (s, s + 1) is the
-  // 16-byte word at row(rg, s) = s RG + 2 rg, and consecutive lanes read
-  // consecutive words.
-  // Columns are taken CPT at a time so that the owner's register slot U is a
-  // compile-time index (a runtime slot would force x out of registers).
-  for (int j0 = 0; j0 < nbr; j0 += CPT) {
-#pragma unroll
-    for (int U = 0; U < CPT; ++U) {
-      const int j = j0 + U;
-      if (j >= nbr) break;
-      double* vb = vbuf[j & 1];
-      if (cg == j0 / CPT) {
-        double s4[4] = {0.0, 0.0, 0.0, 0.0}, av = 0.0;
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const int r = Lay<H>::row(rg, s);
-          if (first) {
-            s4[s & 3] += (r > j) ? x[U][s] * x[U][s] : 0.0;
-            av = (r == j) ? x[U][s] : av;
-          } else {
-            s4[s & 3] += x[U][s] * x[U][s];
-          }
-        }
-        const double ss = group_sum<RG>((s4[0] + s4[1]) + (s4[2] + s4[3]));
-        const double alpha = first ? group_sum<RG>(av) : Rs[j][j];
-        double beta = alpha, tau = 0.0, scale = 1.0;
-        if (ss != 0.0) reflector(alpha, ss, beta, tau, scale);
-        double nv[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const int r = Lay<H>::row(rg, s);
-          const double sc = x[U][s] * scale;
-          if (first) {
-            nv[s] = (r > j) ? sc : ((r == j) ? 1.0 : 0.0);
-            x[U][s] = (r > j) ? sc : ((r == j) ? beta : x[U][s]);
-          } else {
-            nv[s] = sc;
-            x[U][s] = sc;
-          }
-        }
-#pragma unroll
-        for (int s = 0; s < 8; s += 2)
-          *(double2*)&vb[s * RG + 2 * rg] = make_double2(nv[s], nv[s + 1]);
-        if (rg == 0) {
-          taus[j] = tau;
-          if (!first) Rs[j][j] = beta;
-        }
-      }
-      __syncthreads();
-      double v[8];
-#pragma unroll
-      for (int s = 0; s < 8; s += 2) {
-        const double2 p = *(const double2*)&vb[s * RG + 2 * rg];
-        v[s] = p.x;
-        v[s + 1] = p.y;
-      }
-      double d[CPT];
-#pragma unroll
-      for (int u = 0; u < CPT; ++u) {
-        double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-        for (int s = 0; s < 8; s += 2) {
-          a0 += v[s] * x[u][s];
-          a1 += v[s + 1] * x[u][s + 1];
-        }
-        d[u] = a0 + a1;
-      }
-#pragma unroll
-      for (int u = 0; u < CPT; ++u) d[u] = group_sum<RG>(d[u]);
-      const double tau = taus[j];
-#pragma unroll
-      for (int u = 0; u < CPT; ++u) {
-        const int c = cg * CPT + u;
-        if (c > j && c < nbr) {
-          const double w = tau * (first ? d[u] : d[u] + Rs[j][c]);
-#pragma unroll
-          for (int s = 0; s < 8; ++s) x[u][s] -= v[s] * w;
-          if (rg == 0 && !first) Rs[j][c] -= w;
-        } else if (c < j && rg == 0) {
-          Gs[c][j] = d[u];  // v_c . v_j
-        }
-      }
-    }
-  }
-  __syncthreads();
+// Column J of T_b: T[:, J] = -tau_J T[:, :J] G[:J, J] (Sec. 2.3), lane cl
+// holding row cl in t and G[cl, J] in gd (wave 0).
+template <int J>
+__device__ __forceinline__ void t_column(int w, int cl, double (&t)[16], double gd, double tau) {
+  if (w != 0) return;
+  double s0 = 0.0, s1 = 0.0;
+  if constexpr (J > 0) bcast_terms<0>(gd, t, s0, s1);
+  if constexpr (J > 4) bcast_terms<4>(gd, t, s0, s1);
+  if constexpr (J > 8) bcast_terms<8>(gd, t, s0, s1);
+  if constexpr (J > 12) bcast_terms<12>(gd, t, s0, s1);
+  t[J] = cl == J ? tau : -tau * (s0 + s1);
 }
 
-// One pairing level of build_t: for each pair of diagonal blocks of size SZ,
-// T12 = -T1 (G12 T2).  The sums run over whole block rows / columns: the
-// entries outside a triangle are zero in Gs, so no bounds are needed and the
-// loads of a sum can all be in flight together.
-template <int SZ>
-__device__ __forceinline__ void t_pair_level(double (*Gs)[kNB + 1], double* Wt) {
-  constexpr int NP = kNB / (2 * SZ);
-  const int t = threadIdx.x;
-  for (int e = fresh_copy(t); e < NP * SZ * SZ; e += 512) {
-    const int pr = e / (SZ * SZ), i = (e / SZ) % SZ, k = e % SZ;
-    const int a = 2 * SZ * pr, b = a + SZ;
-    double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-    for (int m = 0; m < SZ; m += 2) {
-      s0 += Gs[a + i][b + m] * Gs[b + m][b + k];
-      s1 += Gs[a + i][b + m + 1] * Gs[b + m + 1][b + k];
+// Column J of a sub-panel (b) held in xs (this wave's rows of its 16
+// columns).  first: the pivot row is row J of wave b's tile 0, which is
+// published and cleared, so that the dot products see only the rows below
+// it; stacked: the pivot row is row J of the diagonal tile of R.  t holds row
+// cl of T_b (wave 0), gd and taup the last step's Gram column and tau: column
+// J - 1 of T_b, T[:, j] = -tau_j T[:, :j] G[:j, j] (Sec. 2.3), is formed while
+// the partial sums are exchanged.
+template <int J, int NX>
+__device__ __forceinline__ void node_step(bool first, int b, int w, int g, int cl,
+                                          double (&xs)[NX], double (&t)[16], double& gd,
+                                          double& taup, double& mysc, NodeLds& S) {
+  constexpr int gj = (J >> 1) & 3, rj = ((J >> 3) << 1) | (J & 1), par = J & 1;
+  double* rrowp = &S.r[tri(b, b)][J * kTLD];
+  if (first && w == b) {
+    if (g == gj) {
+      S.prow[par][cl] = xs[rj];
+      xs[rj] = cl >= J ? 0.0 : xs[rj];
     }
-    Wt[e] = s0 + s1;
   }
-  __syncthreads();
-  for (int e = fresh_copy(t); e < NP * SZ * SZ; e += 512) {
-    const int pr = e / (SZ * SZ), i = (e / SZ) % SZ, k = e % SZ;
-    const int a = 2 * SZ * pr, b = a + SZ;
-    const double* w = Wt + pr * SZ * SZ + k;
-    double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-    for (int m = 0; m < SZ; m += 2) {
-      s0 += Gs[a + i][a + m] * w[m * SZ];
-      s1 += Gs[a + i][a + m + 1] * w[(m + 1) * SZ];
-    }
-    Gs[a + i][b + k] = -(s0 + s1);
-  }
-  __syncthreads();
+  double d0 = 0.0, d1 = 0.0;
+  dots_bcast<J>(xs, d0, d1);
+  const double pd = rows_sum(d0 + d1);
+  if (g == 0) S.part[par][cl][w] = pd;
+  // R's row is read before the barrier: wave 1 rewrites it after.
+  double rrow = rrowp[cl];
+  if constexpr (J > 0) t_column<J - 1>(w, cl, t, gd, taup);
+  lds_barrier();
+  const double2 q0 = *(const double2*)&S.part[par][cl][0];
+  const double2 q1 = *(const double2*)&S.part[par][cl][2];
+  if (first) rrow = S.prow[par][cl];
+  const double dot = (q0.x + q0.y) + (q1.x + q1.y);  // x_j . x_cl
+  const double alpha = readlane(rrow, J), sig2 = readlane(dot, J);
+  double bt, tr, z;
+  reflector(alpha, sig2, bt, tr, z);
+  const bool refl = sig2 != 0.0;
+  const double beta = refl ? bt : alpha, sc = refl ? z : 0.0, tau = refl ? tr : 0.0;
+  // v_J . x_cl (v_J has a one in the pivot row); for cl < J it is
+  // v_cl . v_J once scaled.
+  const double wv = rrow + sc * dot;
+  const double tw = tau * wv;
+  const double nf = cl > J ? -(tw * sc) : 0.0;
+  update_bcast<J>(xs, nf);
+  if (w == 1 && g == 0 && cl >= J) rrowp[cl] = cl == J ? beta : rrow - tw;
+  gd = cl < J ? mysc * wv : 0.0;
+  taup = tau;
+  mysc = cl == J ? sc : mysc;
 }
 
-// The same pairing level on FP64 MFMA (SZ = 16 or 32): the two products are
-// (SZ / 16)^2 output tiles per pair, one wave per tile, SZ / 4 k-steps each.
-// Operand layout: a = A[l % 16][l / 16], b = B[l / 16][l % 16],
-// acc[r] = D[l / 16 + 4 r][l % 16].
-template <int SZ>
-__device__ __forceinline__ void t_pair_level_mfma(double (*Gs)[kNB + 1], double* Wt) {
-  constexpr int NP = kNB / (2 * SZ), TPS = SZ / 16, NT = NP * TPS * TPS;
-  static_assert(NT <= 8, "one tile per wave");
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = l >> 4;
-  const int pr = w / (TPS * TPS), ti = (w / TPS) % TPS, tj = w % TPS;
-  const int a = 2 * SZ * pr, b = a + SZ;
-  double* Wp = Wt + pr * SZ * SZ;  // Wt[pr] as SZ x SZ, row-major
-  if (w < NT) {
-    d4 acc = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int ks = 0; ks < SZ / 4; ++ks)
-      acc = mfma64(Gs[a + 16 * ti + li][b + 4 * ks + lk], Gs[b + 4 * ks + lk][b + 16 * tj + li], acc);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) Wp[(16 * ti + lk + 4 * r) * SZ + 16 * tj + li] = acc[r];
-  }
-  __syncthreads();
-  if (w < NT) {
-    d4 acc = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int ks = 0; ks < SZ / 4; ++ks)
-      acc = mfma64(Gs[a + 16 * ti + li][a + 4 * ks + lk], Wp[(4 * ks + lk) * SZ + 16 * tj + li], acc);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) Gs[a + 16 * ti + lk + 4 * r][b + 16 * tj + li] = -acc[r];
-  }
-  __syncthreads();
-}
-
-// T from its 16 x 16 diagonal blocks (in place in Gs) and the Gram entries
-// above them: blocks of 16 and 32 are paired, T12 = -T1 (G12 T2).
-__device__ __forceinline__ void t_from_blocks(double (*Gs)[kNB + 1], double* Wt) {
-  t_pair_level_mfma<16>(Gs, Wt);
-  t_pair_level_mfma<32>(Gs, Wt);
-}
-
-// T in place of the Gram entries left by qr_step (Gs zero below the
-// diagonal and outside nbr).
-__device__ __forceinline__ void build_t(double (*Gs)[kNB + 1], const double* taus, double* Wt,
-                                        int nbr) {
-  const int t = threadIdx.x;
-  // T from the Gram entries G (strict upper part of Gs) and tau (Sec. 2.3:
-  // T^{-1} = striu(V^T V) + diag(tau)^{-1}), built blockwise in place: first
-  // the 8 x 8 diagonal blocks by the column recurrence
-  // T[0:j, j] = -tau_j T[0:j, 0:j] G[0:j, j], taken row by row (row i needs
-  // only its own earlier entries, so each thread builds one row alone), then
-  // blocks of 8, 16, 32 are paired, T12 = -T1 (G12 T2).
-  double Tr[8];
-  const int bb = t >> 3, i = t & 7, r0 = 8 * bb;
-  if (t < kNB) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int col = r0 + j;
-      const double tj = (col < nbr) ? taus[col] : 0.0;
-      double sacc = 0.0;
-#pragma unroll
-      for (int k = 0; k < j; ++k) sacc += Tr[k] * Gs[r0 + k][col];
-      Tr[j] = (i == j) ? tj : ((i < j) ? -tj * sacc : 0.0);
-    }
-  }
-  __syncthreads();
-  if (t < kNB) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (j >= i) Gs[r0 + i][r0 + j] = Tr[j];
-  }
-  __syncthreads();
-  // VALU pairing: the two-workgroups-per-CU leaf kernel that uses this has
-  // no registers to spare for the MFMA form (t_from_blocks).
-  t_pair_level<8>(Gs, Wt);
-  t_pair_level<16>(Gs, Wt);
-  t_pair_level<32>(Gs, Wt);
-}
-
-// LEAF: the chain walks row blocks of the panel (else stacked child R's).
-// PART (leaf only): 0 the whole chain; 1 only its first block (local QR);
-// 2 the blocks after the first, starting from the R that part 1 left in the
-// chain's R slot.  Parts 1 and 2 are separate launches so that part 2, which
-// holds no first-block state, fits two workgroups per CU.
-template <int H, bool LEAF, int PART>
-__device__ __forceinline__ void chain_qr_body(const ChainQRArgs& a) {
-  constexpr int RG = Lay<H>::RG, CPT = Lay<H>::CPT;
-  const int t = threadIdx.x, rg = t % RG, cg = t / RG;
-  const int chain = blockIdx.x;
-  const int b0 = chain * a.chain_len;
-  const int b1 = min(b0 + a.chain_len, a.nblocks);
-  const int nbr = a.nbr;
-  __shared__ double Rs[kNB][kNB + 1];
-  __shared__ double Gs[kNB][kNB + 1];
-  __shared__ __align__(16) double vbuf[2][H];
-  __shared__ double taus[kNB];
-  __shared__ double Wt[32 * kNB / 2];
-
-  {
-    // The starting R (tree: child 0's R; stacked leaf blocks: the chain's R
-    // slot), all loads in flight together (slots are always in bounds),
-    // masked afterwards.
-    const int tt = fresh_copy(t);
-    const double* src = !LEAF ? a.X + (int64_t)b0 * kTS
-                              : (PART == 2 ? a.R + (int64_t)chain * kTS : nullptr);
-    double g[kTS / 512];
-#pragma unroll
-    for (int e = 0; e < kTS / 512; ++e) g[e] = src ? src[tt + 512 * e] : 0.0;
-#pragma unroll
-    for (int e = 0; e < kTS / 512; ++e) {
-      const int i = tt + 512 * e, r = i % kNB, cc = i / kNB;
-      double v = 0.0;
-      if (!LEAF && r < nbr && cc < nbr) v = g[e];
-      if (LEAF && PART == 2 && r <= cc && cc < nbr) v = g[e];
-      Rs[r][cc] = v;
-      Gs[r][cc] = 0.0;
-    }
-  }
-  __syncthreads();
-
-  double x[CPT][8];
-  if constexpr (LEAF) {
-    const int bs = PART == 2 ? b0 + 1 : b0;
-    const int be = PART == 1 ? b0 + 1 : b1;
-    for (int b = bs; b < be; ++b) {
-      const bool first = b == b0;
-      const int64_t rstart = ((int64_t)b * a.xrows) / a.nblocks;
-      const int rows = (int)((((int64_t)b + 1) * a.xrows) / a.nblocks - rstart);
-      double* src = a.X + rstart;
-      const int64_t ld = a.ldx;
-#pragma unroll
-      for (int u = 0; u < CPT; ++u) {
-        const int c = cg * CPT + u;
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-          x[u][s] = (c < nbr && Lay<H>::row(rg, s) < rows)
-                        ? src[Lay<H>::row(rg, s) + (int64_t)c * ld] : 0.0;
-      }
-      if constexpr (PART != 2) {
-        if (first) qr_step<H, true>(x, nbr, Rs, Gs, vbuf, taus, Wt);
-      }
-      if constexpr (PART != 1) {
-        if (!first) qr_step<H, false>(x, nbr, Rs, Gs, vbuf, taus, Wt);
-      }
-#pragma unroll
-      for (int u = 0; u < CPT; ++u) {
-        const int c = cg * CPT + u;
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-          if (c < nbr && Lay<H>::row(rg, s) < rows) src[Lay<H>::row(rg, s) + (int64_t)c * ld] = x[u][s];
-      }
-      build_t(Gs, taus, Wt, nbr);
-      double* Tb = a.T + (int64_t)b * kTS;
-      if (!first) {
-        for (int i = fresh_copy(t); i < kTS; i += 512) {
-          const int r = i % kNB, cc = i / kNB;
-          Tb[i] = (r <= cc && cc < nbr) ? Gs[r][cc] : 0.0;
-        }
-      } else if (PART != 2) {
-        // Z = T V_top^T (upper triangular) in place of T; Rs holds V_top
-        // (unit lower top nbr x nbr part of the block's basis) meanwhile.
-#pragma unroll
-        for (int u = 0; u < CPT; ++u) {
-          const int c = cg * CPT + u;
-#pragma unroll
-          for (int s = 0; s < 8; ++s) {
-            const int r = Lay<H>::row(rg, s);
-            if (r < kNB) Rs[r][c] = (r > c) ? x[u][s] : ((r == c) ? 1.0 : 0.0);
-          }
-        }
-        __syncthreads();
-        for (int i = fresh_copy(t); i < kTS; i += 512) {
-          const int r = i % kNB, cc = i / kNB;
-          double z = 0.0;
-          if (r <= cc && cc < nbr)
-            for (int k = r; k <= cc; ++k) z += Gs[r][k] * Rs[cc][k];
-          Tb[i] = z;
-        }
-        __syncthreads();
-        // The block's R (upper triangle of its top rows) seeds the chain.
-#pragma unroll
-        for (int u = 0; u < CPT; ++u) {
-          const int c = cg * CPT + u;
-#pragma unroll
-          for (int s = 0; s < 8; ++s) {
-            const int r = Lay<H>::row(rg, s);
-            if (r < kNB) Rs[r][c] = (r <= c && c < nbr) ? x[u][s] : 0.0;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  } else if (b1 - b0 >= 2) {
-    // Tree node: children b0+1 .. b1-1 stacked (row stride nbr) under R_{b0}.
-    const int rows = (b1 - b0 - 1) * nbr;
-#pragma unroll
-    for (int u = 0; u < CPT; ++u) {
-      const int c = cg * CPT + u;
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int r = Lay<H>::row(rg, s);
-        double v = 0.0;
-        if (c < nbr && r < rows) {
-          const int sidx = r / nbr, rr = r - sidx * nbr;
-          v = a.X[(int64_t)(b0 + 1 + sidx) * kTS + rr + c * kNB];
-        }
-        x[u][s] = v;
-      }
-    }
-    qr_step<H, false>(x, nbr, Rs, Gs, vbuf, taus, Wt);
-    double* Yn = a.Y + (int64_t)chain * kYS;
-#pragma unroll
-    for (int u = 0; u < CPT; ++u) {
-      const int c = cg * CPT + u;
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int r = Lay<H>::row(rg, s);
-        if (c < nbr && r < rows) Yn[r + c * kYL] = x[u][s];
-      }
-    }
-    build_t(Gs, taus, Wt, nbr);
-    double* Tn = a.T + (int64_t)chain * kTS;
-    for (int i = fresh_copy(t); i < kTS; i += 512) {
-      const int r = i % kNB, cc = i / kNB;
-      Tn[i] = (r <= cc && cc < nbr) ? Gs[r][cc] : 0.0;
-    }
-    __syncthreads();
+template <int J, int NX>
+__device__ __forceinline__ void node_steps(bool first, int b, int w, int g, int cl,
+                                           double (&xs)[NX], double (&t)[16], double& gd,
+                                           double& taup, double& mysc, NodeLds& S) {
+  if constexpr (J < 16) {
+    node_step<J>(first, b, w, g, cl, xs, t, gd, taup, mysc, S);
+    node_steps<J + 1>(first, b, w, g, cl, xs, t, gd, taup, mysc, S);
   } else {
-    double* Tn = a.T + (int64_t)chain * kTS;
-    for (int i = fresh_copy(t); i < kTS; i += 512) Tn[i] = 0.0;
-  }
-
-  for (int i = fresh_copy(t); i < kTS; i += 512) {
-    const int r = i % kNB, cc = i / kNB;
-    a.R[(int64_t)chain * kTS + i] = (r <= cc && cc < nbr) ? Rs[r][cc] : 0.0;
+    t_column<J - 1>(w, cl, t, gd, taup);
   }
 }
 
-// ------------------------------------------------ blocked block QR on MFMA
-//
-// For blocks of 256 rows the column-by-column step above spends most of its
-// issue slots on 32-lane reductions: every reflector is applied to all 64
-// columns at once.  The blocked form (the compact-WY recursion of Sec. 2.3
-// applied inside the block) factors 16-column sub-panels column by column,
-// each column held by half a wave (8 rows per lane, one reduction per
-// column), and applies each sub-panel to the columns right of it with two
-// FP64 MFMA products:  W = V_b^T X,  W' = T_b^T W,  X -= V_b W'.  The same
-// W product, taken over the columns left of the sub-panel too, yields the
-// Gram entries V^T V from which the block's T is built.
-//
-// Register layout ("tile layout"): wave w holds column tile ct = w / 2 and
-// row tiles 8 (w % 2) .. 8 (w % 2) + 7 of the 256 x 64 block; lane (g, cl)
-// (g = l / 16, cl = l % 16) holds rows g + 4 r (r = 0..3) of each 16 x 16
-// tile in column cl, which is the MFMA accumulator layout.  Global rows are
-// staged through the sub-panel buffer P, which also carries each sub-panel
-// between the tile layout and the column-step layout (thread t: column
-// t / 32, rows 8 (t % 32) .. + 7).
-
-constexpr int kPLD = 258;  // column stride of P (doubles)
-
-// Position of row r of a 256-row column in P: rows 8 q + s go to pair q of
-// slice s / 2, so that lanes reading 8 consecutive rows as four pairs hit
-// consecutive 16-byte words.
-__device__ __forceinline__ int ppos(int r) {
-  return ((r & 7) >> 1) * 64 + 2 * (r >> 3) + (r & 1);
-}
-
-struct MfmaQRShared {
-  double P[16][kPLD];        // one 256 x 16 column tile
-  double Wred[8][16][17];    // per-wave partial W tiles (also build_t's scratch)
-  double W[16][kNB + 1];     // W = V_b^T [R; X] of the sub-panel, trailing columns
-  double Wp[16][kNB + 1];    // W' = T_b^T W
-  double Tsub[16][17];
-  __align__(16) double vbuf[2][256];
-};
-
-// Tile-layout coordinates of thread t.
-struct TileCoord {
-  int w, g, cl, ct, rt0;
-  __device__ TileCoord(int t) {
-    w = t >> 6;
-    const int l = t & 63;
-    g = l >> 4;
-    cl = l & 15;
-    ct = w >> 1;
-    rt0 = (w & 1) * 8;
-  }
-  __device__ int row(int k, int r) const { return 16 * (rt0 + k) + g + 4 * r; }
-};
-
-// ppos(16 m + x) = ppos(x) + 4 m for x < 16: a tile's rows sit at a fixed
-// pattern plus 4 per tile, so the k loops below address P as one base per r
-// plus an immediate offset (instead of 32 live addresses).
-__device__ __forceinline__ int tile_base(const TileCoord& tc, int r) {
-  return tc.cl * kPLD + ppos(fresh_copy(tc.g) + 4 * r) + 4 * tc.rt0;
-}
-
-// Move column tile ct_ between the column-step layout in P and the tile
-// registers of its two owner waves.
-__device__ __forceinline__ void tiles_to_p(const TileCoord& tc, int ct_, const double (&xt)[8][4],
-                                           MfmaQRShared& S) {
-  if (tc.ct == ct_)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double* p = &S.P[0][0] + tile_base(tc, r);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) p[4 * k] = xt[k][r];
-    }
-}
-__device__ __forceinline__ void p_to_tiles(const TileCoord& tc, int ct_, double (&xt)[8][4],
-                                           const MfmaQRShared& S) {
-  if (tc.ct == ct_)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double* p = &S.P[0][0] + tile_base(tc, r);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) xt[k][r] = p[4 * k];
-    }
-}
-
-// Column-step layout: thread t holds rows 8 q .. 8 q + 7 (q = t % 32) of
-// column t / 32 of P.
-__device__ __forceinline__ void p_read8(const MfmaQRShared& S, int c, int q, double (&v)[8]) {
-#pragma unroll
-  for (int s = 0; s < 8; s += 2) {
-    const double2 p = *(const double2*)&S.P[c][(s >> 1) * 64 + 2 * q];
-    v[s] = p.x;
-    v[s + 1] = p.y;
-  }
-}
-__device__ __forceinline__ void p_write8(MfmaQRShared& S, int c, int q, const double (&v)[8]) {
-#pragma unroll
-  for (int s = 0; s < 8; s += 2)
-    *(double2*)&S.P[c][(s >> 1) * 64 + 2 * q] = make_double2(v[s], v[s + 1]);
-}
-
-// Load a 256 x 64 block into the tile registers; at(row, col) gives the
-// global element (rows < nrows and cols < nbr only; the rest reads 0).  All
-// global loads are issued before the first exchange through P.
-template <typename At>
-__device__ __forceinline__ void load_block(const TileCoord& tc, double (&xt)[8][4], int nrows,
-                                           int nbr, MfmaQRShared& S, At at) {
-  // Thread (c, q) moves rows q + 32 s of column c: a half-wave covers 32
-  // consecutive rows, so the global accesses coalesce.
-  const int t = threadIdx.x, c = t >> 5, q = t & 31;
-  double v[4][8];
-#pragma unroll
-  for (int ct_ = 0; ct_ < 4; ++ct_) {
-    const int col = 16 * ct_ + c;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      // Clamped into the valid corner and masked after the load, so that no
-      // load waits on a predicate and all of them are in flight together.
-      const int row = q + 32 * s;
-      const double g = at(min(row, nrows - 1), min(col, nbr - 1));
-      v[ct_][s] = (col < nbr && row < nrows) ? g : 0.0;
-    }
-  }
-#pragma unroll
-  for (int ct_ = 0; ct_ < 4; ++ct_) {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) S.P[c][ppos(q + 32 * s)] = v[ct_][s];
-    __syncthreads();
-    p_to_tiles(tc, ct_, xt, S);
-    __syncthreads();
-  }
-}
-
-// Store the tile registers; put(row, col, value) for rows < nrows, cols < nbr.
-// The global stores are issued after the last exchange through P, so that no
-// barrier waits for them.
-template <typename Put>
-__device__ __forceinline__ void store_block(const TileCoord& tc, const double (&xt)[8][4],
-                                            int nrows, int nbr, MfmaQRShared& S, Put put) {
-  const int t = threadIdx.x, c = t >> 5, q = t & 31;
-  double v[4][8];
-#pragma unroll
-  for (int ct_ = 0; ct_ < 4; ++ct_) {
-    tiles_to_p(tc, ct_, xt, S);
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < 8; ++s) v[ct_][s] = S.P[c][ppos(q + 32 * s)];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int ct_ = 0; ct_ < 4; ++ct_) {
-    const int col = 16 * ct_ + c;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int row = q + 32 * s;
-      if (col < nbr && row < nrows) put(row, col, v[ct_][s]);
-    }
-  }
-}
-
-// Sum over the 32 lanes of a half-wave, result in every lane: the 16-lane
-// sums of group_sum, then the two rows exchanged in registers by
-// v_permlane16_swap (one copy ends up holding the even row in both rows, the
-// other the odd row) instead of a ds_swizzle round trip through the LDS unit.
-__device__ __forceinline__ double half_wave_sum(double v) {
-  v = group_sum<16>(v);
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)(u & 0xffffffffull), hi = (unsigned)(u >> 32);
-  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  const double e =
-      __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | (unsigned long long)l[0]));
-  const double o =
-      __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | (unsigned long long)l[1]));
-  return e + o;
-}
-
-// Column jp of T_b (Sec. 2.3 recurrence, T[0:jp, jp] = -tau_jp T[0:jp, 0:jp]
-// G[0:jp, jp]), entry of row i.  Row i of T_b was cleared at the start of the
-// sub-panel, so the sum can run over all 16 terms: T[i][k] is zero for k < i
-// and for k >= jp (not built yet), and G is zero below its diagonal, where
-// only zero T entries meet it.  No bounds, so the loads overlap.
-__device__ __forceinline__ void tsub_column(MfmaQRShared& S, double (*Gs)[kNB + 1],
-                                            const double* taus, int b, int jp, int i) {
-  if (jp < 0) return;
-  const int jv = 16 * b + jp;
-  const double tj = taus[jv];
-  double p0 = 0.0, p1 = 0.0;
-#pragma unroll
-  for (int k = 0; k < 16; k += 2) {
-    p0 += S.Tsub[i][k] * Gs[16 * b + k][jv];
-    p1 += S.Tsub[i][k + 1] * Gs[16 * b + k + 1][jv];
-  }
-  S.Tsub[i][jp] = (i == jp) ? tj : ((i < jp) ? -tj * (p0 + p1) : 0.0);
-}
-
-// Blocked Householder QR of the block in xt (first: the rows themselves;
-// else stacked under the upper triangular R in Rs).  On return xt holds the
-// basis (first: R on and above the diagonal of the top rows), Rs the new R
-// (stacked), Gs the Gram entries v_i . v_j (i < j) in its strict upper part,
-// taus the reflector scalars.  Gs must be zero elsewhere, taus zero beyond
-// nbr.
-template <bool first>
-__device__ void mfma_block_qr(const TileCoord& tc, double (&xt)[8][4], int nbr,
-                              double (*Rs)[kNB + 1], double (*Gs)[kNB + 1], double* taus,
-                              MfmaQRShared& S) {
-  const int t = threadIdx.x, c = t >> 5, q = t & 31;
+// Householder QR of the block in x (x[c][t]: column tile c, row tile t of this
+// wave).  On return x holds the basis (zero above and one on the diagonal of
+// a first block), S.r the new R, S.t the block's T (both after a barrier).
+// TRI (tree nodes): the stacked rows are upper triangular children, one per
+// wave, so row tiles below the sub-panel's diagonal are zero and skipped.
+// first: S.r zero on entry, tile 0 of wave w holds rows 16 w .. 16 w + 15.
+template <int RT, bool TRI>
+__device__ __forceinline__ void node_qr(bool first, d4 (&x)[4][RT], int nbr, int w, NodeLds& S) {
   const int nsub = (nbr + 15) >> 4;
   for (int b = 0; b < nsub; ++b) {
-    // Sub-panel b into the column-step layout; T_b cleared (its rows are
-    // built during the column steps).
-    tiles_to_p(tc, b, xt, S);
-    if (t < 16 * 17) (&S.Tsub[0][0])[t] = 0.0;
-    __syncthreads();
-    const int jc = 16 * b + c;
-    double xf[8];
-    p_read8(S, c, q, xf);
-    for (int j = 0; j < 16; ++j) {
-      const int jg = 16 * b + j;
-      if (jg >= nbr) break;
-      double* vb = S.vbuf[j & 1];
-      if (c == j) {
-        double s4[4] = {0.0, 0.0, 0.0, 0.0}, av = 0.0;
+    const int pw = min(16, nbr - 16 * b), bb = tri(b, b);
+    double mysc = 0.0;
+    {
+      const int l = lane_id(), g = l >> 4, cl = l & 15;
+      double xs[4 * RT], t[16], gd = 0.0, taup = 0.0;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const int r = 8 * q + s;
-          if (first) {
-            s4[s & 3] += (r > jg) ? xf[s] * xf[s] : 0.0;
-            av = (r == jg) ? xf[s] : av;
-          } else {
-            s4[s & 3] += xf[s] * xf[s];
-          }
-        }
-        const double ss = half_wave_sum((s4[0] + s4[1]) + (s4[2] + s4[3]));
-        const double alpha = first ? half_wave_sum(av) : Rs[jg][jg];
-        double beta = alpha, tau = 0.0, scale = 1.0;
-        if (ss != 0.0) reflector(alpha, ss, beta, tau, scale);
-        double nv[8];
+      for (int k = 0; k < RT; ++k)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const int r = 8 * q + s;
-          const double sc = xf[s] * scale;
-          if (first) {
-            nv[s] = (r > jg) ? sc : ((r == jg) ? 1.0 : 0.0);
-            xf[s] = (r > jg) ? sc : ((r == jg) ? beta : xf[s]);
-          } else {
-            nv[s] = sc;
-            xf[s] = sc;
-          }
-        }
+        for (int r = 0; r < 4; ++r) xs[4 * k + r] = x[0][k][r];
 #pragma unroll
-        for (int s = 0; s < 8; s += 2)
-          *(double2*)&vb[(s >> 1) * 64 + 2 * q] = make_double2(nv[s], nv[s + 1]);
-        if (q == 0) {
-          taus[jg] = tau;
-          if (!first) Rs[jg][jg] = beta;
-        }
+      for (int k = 0; k < 16; ++k) t[k] = 0.0;
+      node_steps<0>(first, b, w, g, cl, xs, t, gd, taup, mysc, S);
+      if (w == 0 && g == 0) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) S.t[bb][cl * kTLD + k] = t[k];
       }
-      __syncthreads();
-      if (c > j && jc < nbr) {
-        double v[8];
 #pragma unroll
-        for (int s = 0; s < 8; s += 2) {
-          const double2 p = *(const double2*)&vb[(s >> 1) * 64 + 2 * q];
-          v[s] = p.x;
-          v[s + 1] = p.y;
-        }
-        double a0 = 0.0, a1 = 0.0;
+      for (int k = 0; k < RT; ++k)
 #pragma unroll
-        for (int s = 0; s < 8; s += 2) {
-          a0 += v[s] * xf[s];
-          a1 += v[s + 1] * xf[s + 1];
-        }
-        const double d = half_wave_sum(a0 + a1);
-        const double wv = taus[jg] * (first ? d : d + Rs[jg][jc]);
+        for (int r = 0; r < 4; ++r) x[0][k][r] = xs[4 * k + r] * mysc;
+      if (first && w == b && cl < pw) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) xf[s] -= v[s] * wv;
-        if (!first && q == 0) Rs[jg][jc] -= wv;
-      } else if (c < j) {
-        // Columns left of the pivot are final: their half-waves form the
-        // Gram entries v_c . v_j (v_j is zero above its pivot row, where a
-        // first block's column still holds R), and half-wave 0 builds
-        // column j - 1 of T_b, whose Gram column is complete.
-        double v[8];
-#pragma unroll
-        for (int s = 0; s < 8; s += 2) {
-          const double2 p = *(const double2*)&vb[(s >> 1) * 64 + 2 * q];
-          v[s] = p.x;
-          v[s + 1] = p.y;
-        }
-        double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-        for (int s = 0; s < 8; s += 2) {
-          a0 += v[s] * xf[s];
-          a1 += v[s + 1] * xf[s + 1];
-        }
-        const double d = half_wave_sum(a0 + a1);
-        if (q == 0) Gs[jc][jg] = d;
-        if (c == 0 && q < 16) tsub_column(S, Gs, taus, b, j - 1, q);
+        for (int r = 0; r < 4; ++r)
+          x[0][0][r] = (8 * (r >> 1) + 2 * g + (r & 1) == cl) ? 1.0 : x[0][0][r];
       }
     }
-    // The factored sub-panel back into P and into its owners' tiles.
-    p_write8(S, c, q, xf);
-    __syncthreads();
-    p_to_tiles(tc, b, xt, S);
-    if (t < 16) tsub_column(S, Gs, taus, b, min(16, nbr - 16 * b) - 1, t);
-
-    // Partial W = V_b^T X over this wave's 128 rows, all column tiles (the
-    // tiles left of b and b itself give Gram entries, the rest the update).
-    // MFMA operands: A = V_b^T (lane: V_b[row][16 b + cl]), B = X (lane:
-    // xt[k][r]); the k index of the product runs over rows g + 4 r.
-    d4 acc = d4{0.0, 0.0, 0.0, 0.0};
-    if (16 * tc.ct < nbr) {
+    // Slot s holds column tile (b + s) mod 4: right of the sub-panel while
+    // b + s < 4 (absent beyond nbr), left of it (basis already) otherwise.
+    const int nright = nsub - b;  // slots 1 .. nright - 1 are right of it
+    const int l = lane_id(), g = l >> 4, cl = l & 15;
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+      if (s < nright || s >= 4 - b) {
+        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < RT; ++k) {
+          if (!TRI || k <= b) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc = mfma64(x[0][k][r], x[s][k][r], acc);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S.red[w][s - 1][(g + 4 * r) * kTLD + cl] = acc[r];
+      }
+    }
+    lds_barrier();
+    // Wave s adds slot s's partial products.  Right of the sub-panel:
+    // W = V_b^T X (+ R's rows), W' = T_b^T W, R's rows lose W'.  Left of it:
+    // V_b^T V_q = G^T, kept as G T_b for T's block column b.
+    if (w > 0 && (w < nright || w >= 4 - b)) {
+      const int c = (b + w) & 3;
+      double v[4], tb[4];
+      d4 o = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const double* pv = &S.P[0][0] + tile_base(tc, r);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          double av = pv[4 * k];
-          double bx = xt[k][r];
-          if (first) {
-            const int row = tc.row(k, r);
-            const int vc = 16 * b + tc.cl, xc = 16 * tc.ct + tc.cl;
-            av = (row < vc) ? 0.0 : ((row == vc) ? 1.0 : av);
-            if (tc.ct <= b) bx = (row < xc) ? 0.0 : ((row == xc) ? 1.0 : bx);
-          }
-          acc = mfma64(av, bx, acc);
-        }
+        const int e = (g + 4 * r) * kTLD + cl;
+        v[r] = (S.red[0][w - 1][e] + S.red[1][w - 1][e]) + (S.red[2][w - 1][e] + S.red[3][w - 1][e]);
+        tb[r] = S.t[bb][e];
       }
-    }
+      if (w < nright) {
+        double* rt = S.r[tri(b, c)];
+        double rv[4];
+        if (!first) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) S.Wred[tc.w][tc.g + 4 * r][tc.cl] = acc[r];
-    __syncthreads();
-    for (int e = fresh_copy(t); e < 16 * kNB; e += 512) {
-      const int m = e & 15, col = e >> 4, ct_ = col >> 4, n = col & 15;
-      const int jv = 16 * b + m;
-      const double val = S.Wred[2 * ct_][m][n] + S.Wred[2 * ct_ + 1][m][n];
-      if (ct_ < b) {
-        if (jv < nbr) Gs[col][jv] = val;
-      } else if (ct_ > b) {
-        S.W[m][col] = val + ((first || jv >= nbr || col >= nbr) ? 0.0 : Rs[jv][col]);
-      }
-    }
-    // T_b into the diagonal block of Gs (its Gram entries are used up).
-    if (t < 256) {
-      const int i = t >> 4, jj = t & 15;
-      if (i <= jj) Gs[16 * b + i][16 * b + jj] = S.Tsub[i][jj];
-    }
-    __syncthreads();
-    if (16 * (b + 1) >= nbr) continue;  // no columns right of the last sub-panel
-    // W' = T_b^T W on the trailing columns; R rows of the sub-panel (stacked).
-    for (int e = fresh_copy(t); e < 16 * kNB; e += 512) {
-      const int m = e & 15, col = e >> 4;
-      if (col < 16 * (b + 1)) continue;
-      double sacc = 0.0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) sacc += S.Tsub[k][m] * S.W[k][col];  // T_b upper: 0 for k > m
-      S.Wp[m][col] = sacc;
-      if (!first && 16 * b + m < nbr && col < nbr) Rs[16 * b + m][col] -= sacc;
-    }
-    __syncthreads();
-    // X -= V_b W' on the column tiles right of b.  A = V_b (lane: V_b[row
-    // 16 (rt0 + k) + cl][16 b + 4 p + g]), B = W' (lane: W'[4 p + g][16 ct + cl]).
-    if (tc.ct > b && 16 * tc.ct < nbr) {
-      // Row 16 (rt0 + k) + cl of column 4 p + g of P sits at
-      // pa + 4 k + 4 p kPLD; W'[4 p + g][16 ct + cl] at pw + 4 p (kNB + 1).
-      const double* pa = &S.P[0][0] + fresh_copy(tc.g) * kPLD + ppos(tc.cl) + 4 * tc.rt0;
-      const double* pw = &S.Wp[0][0] + fresh_copy(tc.g) * (kNB + 1) + 16 * tc.ct + tc.cl;
-      double wp[4];
-#pragma unroll
-      for (int p = 0; p < 4; ++p) wp[p] = -pw[4 * p * (kNB + 1)];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        d4 xa = d4{xt[k][0], xt[k][1], xt[k][2], xt[k][3]};
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          double av = pa[4 * k + 4 * p * kPLD];
-          if (first) {
-            const int row = 16 * (tc.rt0 + k) + tc.cl, vc = 16 * b + 4 * p + tc.g;
-            av = (row < vc) ? 0.0 : ((row == vc) ? 1.0 : av);
+          for (int r = 0; r < 4; ++r) {
+            rv[r] = rt[(g + 4 * r) * kTLD + cl];
+            v[r] += rv[r];
           }
-          xa = mfma64(av, wp[p], xa);
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) xt[k][r] = xa[r];
+        for (int r = 0; r < 4; ++r) o = mfma64(tb[r], v[r], o);
+        if (!first) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) rt[(g + 4 * r) * kTLD + cl] = rv[r] - o[r];
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o = mfma64(v[r], tb[r], o);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) S.wp[w - 1][(g + 4 * r) * kTLD + cl] = o[r];
+    }
+    lds_barrier();
+    if (nright > 1) {
+      // X -= V_b W' on the slots right of the sub-panel.
+      double wn[3][4];
+#pragma unroll
+      for (int s = 1; s < 4; ++s)
+        if (s < nright) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p) wn[s - 1][p] = -S.wp[s - 1][(g + 4 * p) * kTLD + cl];
+        }
+#pragma unroll
+      for (int k = 0; k < RT; ++k) {
+        if (!TRI || k <= b) {
+          double* vt = S.red[w][k % 3];
+          double va[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) vt[(g + 4 * r) * kTLD + cl] = x[0][k][r];
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int p = 0; p < 4; ++p) va[p] = vt[cl * kTLD + g + 4 * p];
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int s = 1; s < 4; ++s)
+            if (s < nright) {
+#pragma unroll
+              for (int p = 0; p < 4; ++p) x[s][k] = mfma64(va[p], wn[s - 1][p], x[s][k]);
+            }
+        }
+      }
+      if (first && w == b) {
+        // Rows 16 b .. of the tiles right of the sub-panel are rows of R.
+#pragma unroll
+        for (int s = 1; s < 4; ++s)
+          if (s < nright) {
+            double* rt = S.r[tri(b, b + s)];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              rt[(8 * (r >> 1) + 2 * g + (r & 1)) * kTLD + cl] = x[s][0][r];
+              x[s][0][r] = 0.0;
+            }
+          }
       }
     }
-    __syncthreads();
+    // Block column b of T: T_pb = -sum_q T_pq (G_qb T_b), q = p .. b - 1, wave p.
+    if (w < b) {
+      d4 o = d4{0.0, 0.0, 0.0, 0.0};
+      for (int q = w; q < b; ++q) {
+        const double* tq = S.t[tri(w, q)];
+        const double* hq = S.wp[q + 3 - b];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          o = mfma64(tq[cl * kTLD + g + 4 * r], hq[(g + 4 * r) * kTLD + cl], o);
+      }
+      double* tp = S.t[tri(w, b)];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) tp[(g + 4 * r) * kTLD + cl] = -o[r];
+    }
+    // Rotate the slots: the next sub-panel to slot 0.
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      const d4 x0 = x[0][k];
+      x[0][k] = x[1][k];
+      x[1][k] = x[2][k];
+      x[2][k] = x[3][k];
+      x[3][k] = x0;
+    }
+  }
+  for (int b = nsub; b < 4; ++b) {
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      const d4 x0 = x[0][k];
+      x[0][k] = x[1][k];
+      x[1][k] = x[2][k];
+      x[2][k] = x[3][k];
+      x[3][k] = x0;
+    }
   }
 }
 
-// Chain / node body for 256-row blocks on the blocked MFMA factorisation
-// (same roles of LEAF and PART as chain_qr_body).
-template <bool LEAF, int PART>
-__device__ __forceinline__ void chain_qr_body_mfma(const ChainQRArgs& a) {
-  const int t = threadIdx.x;
-  const TileCoord tc(t);
-  const int chain = blockIdx.x;
-  const int b0 = chain * a.chain_len;
+// Two adjacent rows of a column; matrices need not be 16-byte aligned.
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// Rows row, row + 1 (row even) of a column with nrows rows, zero beyond them;
+// nothing outside rows 0 .. nrows - 1 is read.
+__device__ __forceinline__ void load_pair(const double* col, int row, int nrows, bool in,
+                                          double& v0, double& v1) {
+  if (nrows >= 2) {
+    const d2u v = *(const d2u*)(col + min(row, nrows - 2));
+    v0 = in ? (row + 1 < nrows ? v[0] : (row < nrows ? v[1] : 0.0)) : 0.0;
+    v1 = (in && row + 1 < nrows) ? v[1] : 0.0;
+  } else {
+    const double v = col[0];
+    v0 = (in && row == 0) ? v : 0.0;
+    v1 = 0.0;
+  }
+}
+__device__ __forceinline__ void store_pair(double* col, int row, int nrows, double v0, double v1) {
+  if (row + 1 < nrows) {
+    d2u v;
+    v[0] = v0;
+    v[1] = v1;
+    *(d2u*)(col + row) = v;
+  } else if (row < nrows) {
+    col[row] = v0;
+  }
+}
+
+// An nbr x nbr upper triangle from the tiles in LDS to a slot (column-major,
+// leading dim kNB), zero elsewhere.
+__device__ __forceinline__ void store_triangle(const double (*S)[kTile], double* G, int nbr) {
+  for (int i = threadIdx.x; i < kTS; i += 256) {
+    const int r = i % kNB, c = i / kNB;
+    double v = 0.0;
+    if (r <= c && c < nbr) v = S[tri(r >> 4, c >> 4)][(r & 15) * kTLD + (c & 15)];
+    G[i] = v;
+  }
+}
+// And back: tiles of the upper triangle of a slot (its entries outside the
+// triangle and beyond nbr are replaced by zero).
+__device__ __forceinline__ void load_triangle(double (*S)[kTile], const double* G, int nbr) {
+  double g[kTS / 256];
+#pragma unroll
+  for (int e = 0; e < kTS / 256; ++e) g[e] = G[threadIdx.x + 256 * e];
+#pragma unroll
+  for (int e = 0; e < kTS / 256; ++e) {
+    const int i = threadIdx.x + 256 * e, r = i % kNB, c = i / kNB;
+    if ((r >> 4) <= (c >> 4))
+      S[tri(r >> 4, c >> 4)][(r & 15) * kTLD + (c & 15)] = (r <= c && c < nbr) ? g[e] : 0.0;
+  }
+}
+
+// Leaf chains: the blocks of a chain in sequence, the first by itself, every
+// later one stacked under the running R, which stays in LDS.  RT row tiles per
+// wave: blocks of up to 64 RT rows.
+template <int RT>
+__global__ __launch_bounds__(256, 2) void k_tsqr_leaf(ChainQRArgs a) {
+  __shared__ NodeLds S;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b0 = blockIdx.x * a.chain_len;
   const int b1 = min(b0 + a.chain_len, a.nblocks);
   const int nbr = a.nbr;
-  __shared__ double Rs[kNB][kNB + 1];
-  __shared__ double Gs[kNB][kNB + 1];
-  __shared__ double taus[kNB];
-  __shared__ MfmaQRShared S;
-  double* Wt = &S.Wred[0][0][0];
-
-  {
-    // The starting R (tree: child 0's R; stacked leaf blocks: the chain's R
-    // slot), all loads in flight together (slots are always in bounds),
-    // masked afterwards.
-    const int tt = fresh_copy(t);
-    const double* src = !LEAF ? a.X + (int64_t)b0 * kTS
-                              : (PART == 2 ? a.R + (int64_t)chain * kTS : nullptr);
-    double g[kTS / 512];
+  d4 x[4][RT];
+  for (int i = threadIdx.x; i < 10 * kTile; i += 256) (&S.r[0][0])[i] = 0.0;
+  for (int b = b0; b < b1; ++b) {
+    const bool first = b == b0;
+    const int l = lane_id(), g = l >> 4, cl = l & 15;
+    const int64_t rstart = ((int64_t)b * a.xrows) / a.nblocks;
+    const int rows = (int)((((int64_t)b + 1) * a.xrows) / a.nblocks - rstart);
+    double* src = a.X + rstart;
+    // First row of this wave's row tile k: a first block keeps its top 64
+    // rows (where the pivots are) one tile per wave.
+    auto row0 = [&](int k) {
+      return first ? (k == 0 ? 16 * w : 64 + 16 * (w * (RT - 1) + k - 1)) : 16 * (w * RT + k);
+    };
 #pragma unroll
-    for (int e = 0; e < kTS / 512; ++e) g[e] = src ? src[tt + 512 * e] : 0.0;
+    for (int c = 0; c < 4; ++c) {
+      const int col = 16 * c + cl;
+      const double* cp = src + (int64_t)min(col, nbr - 1) * a.ldx;
 #pragma unroll
-    for (int e = 0; e < kTS / 512; ++e) {
-      const int i = tt + 512 * e, r = i % kNB, cc = i / kNB;
-      double v = 0.0;
-      if (!LEAF && r < nbr && cc < nbr) v = g[e];
-      if (LEAF && PART == 2 && r <= cc && cc < nbr) v = g[e];
-      Rs[r][cc] = v;
-      Gs[r][cc] = 0.0;
+      for (int k = 0; k < RT; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          double v0, v1;
+          load_pair(cp, row0(k) + 8 * h + 2 * g, rows, col < nbr, v0, v1);
+          x[c][k][2 * h] = v0;
+          x[c][k][2 * h + 1] = v1;
+        }
     }
-  }
-  if (t < kNB) taus[t] = 0.0;
-  __syncthreads();
-
-  double xt[8][4];
-  if constexpr (LEAF) {
-    const int bs = PART == 2 ? b0 + 1 : b0;
-    const int be = PART == 1 ? b0 + 1 : b1;
-    for (int b = bs; b < be; ++b) {
-      const bool first = b == b0;
-      const int64_t rstart = ((int64_t)b * a.xrows) / a.nblocks;
-      const int rows = (int)((((int64_t)b + 1) * a.xrows) / a.nblocks - rstart);
-      double* src = a.X + rstart;
-      const int64_t ld = a.ldx;
-      load_block(tc, xt, rows, nbr, S,
-                 [&](int row, int col) { return src[row + (int64_t)col * ld]; });
-      if constexpr (PART != 2) {
-        if (first) mfma_block_qr<true>(tc, xt, nbr, Rs, Gs, taus, S);
+    lds_barrier();  // R of the last block (or its zeros) is in LDS
+    node_qr<RT, false>(first, x, nbr, w, S);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int col = 16 * c + cl;
+      double* cp = src + (int64_t)col * a.ldx;
+      if (col < nbr) {
+#pragma unroll
+        for (int k = 0; k < RT; ++k)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            store_pair(cp, row0(k) + 8 * h + 2 * g, rows, x[c][k][2 * h], x[c][k][2 * h + 1]);
       }
-      if constexpr (PART != 1) {
-        if (!first) mfma_block_qr<false>(tc, xt, nbr, Rs, Gs, taus, S);
-      }
-      store_block(tc, xt, rows, nbr, S,
-                  [&](int row, int col, double v) { src[row + (int64_t)col * ld] = v; });
-      t_from_blocks(Gs, Wt);
-      double* Tb = a.T + (int64_t)b * kTS;
-      if (!first) {
-        for (int i = fresh_copy(t); i < kTS; i += 512) {
-          const int r = i % kNB, cc = i / kNB;
-          Tb[i] = (r <= cc && cc < nbr) ? Gs[r][cc] : 0.0;
-        }
-      } else if (PART != 2) {
-        // Z = T V_top^T (upper triangular) in place of T; Rs holds V_top
-        // (unit lower top nbr x nbr part of the block's basis) meanwhile.
-        if (tc.rt0 == 0) {
+    }
+    lds_barrier();  // T is complete
+    double* Tb = a.T + (int64_t)b * kTS;
+    if (!first) {
+      store_triangle(S.t, Tb, nbr);
+    } else {
+      // Z = T V_top^T (upper triangular) in place of T.  Wave c forms block
+      // column c, Z_pc = sum_q T_pq V_cq^T; V_cq is its own row tile 0.
+      d4 z[4];
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
+      for (int p = 0; p < 4; ++p) z[p] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int row = tc.row(k, r), col = 16 * tc.ct + tc.cl;
-              Rs[row][col] = (row > col) ? xt[k][r] : ((row == col) ? 1.0 : 0.0);
-            }
-        }
-        __syncthreads();
-        for (int i = fresh_copy(t); i < kTS; i += 512) {
-          const int r = i % kNB, cc = i / kNB;
-          double z = 0.0;
-          if (r <= cc && cc < nbr)
-            for (int k = r; k <= cc; ++k) z += Gs[r][k] * Rs[cc][k];
-          Tb[i] = z;
-        }
-        __syncthreads();
-        // The block's R (upper triangle of its top rows) seeds the chain.
-        if (tc.rt0 == 0) {
+      for (int q = 0; q < 4; ++q) {
+        if (q <= w) {
+          double* vt = S.red[w][0];
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
+          for (int r = 0; r < 4; ++r)
+            vt[(8 * (r >> 1) + 2 * g + (r & 1)) * kTLD + cl] = x[q][0][r];
+          __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int row = tc.row(k, r), col = 16 * tc.ct + tc.cl;
-              Rs[row][col] = (row <= col && col < nbr) ? xt[k][r] : 0.0;
-            }
+          for (int r = 0; r < 4; ++r) {
+            const double bv = vt[cl * kTLD + g + 4 * r];
+#pragma unroll
+            for (int p = 0; p <= q; ++p)
+              z[p] = mfma64(S.t[tri(p, q)][cl * kTLD + g + 4 * r], bv, z[p]);
+          }
+          __builtin_amdgcn_wave_barrier();
         }
       }
-      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * p + g + 4 * r, col = 16 * w + cl;
+          Tb[row + col * kNB] = (row <= col && col < nbr) ? z[p][r] : 0.0;
+        }
     }
-  } else if (b1 - b0 >= 2) {
-    // Tree node: children b0+1 .. b1-1 stacked (row stride nbr) under R_{b0}.
-    const int rows = (b1 - b0 - 1) * nbr;
-    const double* X = a.X;
-    // Child index of a stacked row by a float reciprocal: (row + 1/2) / nbr
-    // is never within 1/(2 nbr) of an integer, far above float rounding.
-    const float inv_nbr = 1.0f / (float)nbr;
-    load_block(tc, xt, rows, nbr, S, [&](int row, int col) {
-      const int sidx = (int)(((float)row + 0.5f) * inv_nbr), rr = row - sidx * nbr;
-      return X[(int64_t)(b0 + 1 + sidx) * kTS + rr + col * kNB];
-    });
-    mfma_block_qr<false>(tc, xt, nbr, Rs, Gs, taus, S);
-    double* Yn = a.Y + (int64_t)chain * kYS;
-    store_block(tc, xt, rows, nbr, S,
-                [&](int row, int col, double v) { Yn[row + col * kYL] = v; });
-    t_from_blocks(Gs, Wt);
-    double* Tn = a.T + (int64_t)chain * kTS;
-    for (int i = fresh_copy(t); i < kTS; i += 512) {
-      const int r = i % kNB, cc = i / kNB;
-      Tn[i] = (r <= cc && cc < nbr) ? Gs[r][cc] : 0.0;
-    }
-    __syncthreads();
-  } else {
-    double* Tn = a.T + (int64_t)chain * kTS;
-    for (int i = fresh_copy(t); i < kTS; i += 512) Tn[i] = 0.0;
   }
-
-  for (int i = fresh_copy(t); i < kTS; i += 512) {
-    const int r = i % kNB, cc = i / kNB;
-    a.R[(int64_t)chain * kTS + i] = (r <= cc && cc < nbr) ? Rs[r][cc] : 0.0;
-  }
+  lds_barrier();
+  store_triangle(S.r, a.R + (int64_t)blockIdx.x * kTS, nbr);
 }
 
-template <int H, bool LEAF, int PART>
-__global__ __launch_bounds__(512) void k_chain_qr(ChainQRArgs a) {
-  if constexpr (H == 256) chain_qr_body_mfma<LEAF, PART>(a);
-  else chain_qr_body<H, LEAF, PART>(a);
-}
-
-// Blocks after the first of each leaf chain, at two workgroups per CU.  This
-// launch has enough chains to fill the chip twice over, so it keeps the
-// column-by-column body, which fits two workgroups per CU; the blocked body
-// needs 140 KB of LDS (one workgroup per CU) and only pays off where a CU has
-// one workgroup anyway (tree nodes, first blocks).
-template <int H>
-__global__ __launch_bounds__(512, 4) void k_chain_qr_rest(ChainQRArgs a) {
-  chain_qr_body<H, true, 2>(a);
+// Tree nodes: the R factors of children 1 .. k - 1 stacked under child 0's.
+// TRI: one child per wave (k <= 5), its triangle kept in place; else the
+// children's rows packed one after the other (narrow panels with wide nodes).
+template <bool TRI>
+__global__ __launch_bounds__(256, 2) void k_tsqr_tree(ChainQRArgs a) {
+  __shared__ NodeLds S;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l = lane_id(), g = l >> 4, cl = l & 15;
+  const int node = blockIdx.x;
+  const int b0 = node * a.chain_len;
+  const int k1 = min(a.chain_len, a.nblocks - b0) - 1;  // stacked children
+  const int nbr = a.nbr;
+  double* Tn = a.T + (int64_t)node * kTS;
+  double* Rn = a.R + (int64_t)node * kTS;
+  if (k1 == 0) {
+    const double* R0 = a.X + (int64_t)b0 * kTS;
+    for (int i = threadIdx.x; i < kTS; i += 256) {
+      Tn[i] = 0.0;
+      Rn[i] = R0[i];
+    }
+    return;
+  }
+  d4 x[4][4];
+  const int rows = k1 * nbr;
+  const double* child = a.X + (int64_t)(b0 + 1 + min(w, k1 - 1)) * kTS;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int col = 16 * c + cl;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (TRI) {
+        if (k > c) {
+          x[c][k] = d4{0.0, 0.0, 0.0, 0.0};
+          continue;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int row = 16 * k + 8 * h + 2 * g;
+          const d2u v = *(const d2u*)(child + row + col * kNB);
+          const bool in = w < k1 && col < nbr;
+          x[c][k][2 * h] = (in && row <= col) ? v[0] : 0.0;
+          x[c][k][2 * h + 1] = (in && row + 1 <= col) ? v[1] : 0.0;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * (4 * w + k) + 8 * (r >> 1) + 2 * g + (r & 1);
+          const int ch = min(row / nbr, k1 - 1), rr = min(row - ch * nbr, nbr - 1);
+          const double v = a.X[(int64_t)(b0 + 1 + ch) * kTS + rr + min(col, nbr - 1) * kNB];
+          x[c][k][r] = (row < rows && col < nbr) ? v : 0.0;
+        }
+      }
+    }
+  }
+  load_triangle(S.r, a.X + (int64_t)b0 * kTS, nbr);
+  lds_barrier();
+  node_qr<4, TRI>(false, x, nbr, w, S);
+  double* Yn = a.Y + (int64_t)node * kYS;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int col = 16 * c + cl;
+    if (col >= nbr) continue;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int row = 16 * (TRI ? k : 4 * w + k) + 8 * h + 2 * g;
+        if (TRI) {
+          if (w < k1) store_pair(Yn + w * nbr + col * kYL, row, nbr, x[c][k][2 * h], x[c][k][2 * h + 1]);
+        } else {
+          store_pair(Yn + col * kYL, row, rows, x[c][k][2 * h], x[c][k][2 * h + 1]);
+        }
+      }
+  }
+  lds_barrier();
+  store_triangle(S.t, Tn, nbr);
+  store_triangle(S.r, Rn, nbr);
 }
 
 struct HRArgs {
@@ -1556,42 +1123,25 @@ hipError_t tsqr_factor(const TsqrPlan& p, hipStream_t s, double* P, int64_t ldp,
     const TsqrLevel& l0 = p.levels[0];
     ChainQRArgs a{P, ldp, p.rows, l0.nblocks, l0.chain_len, nbr, nullptr, l0.T, l0.R};
     // Read A, write V; write T per block and R per chain.  Flops: QR 2 m nb^2
-    // plus the Gram products for T, m nb^2.  First blocks and the rest of
-    // each chain are separate launches; the byte and flop counts are split
-    // by the share of rows.
-    const double f1 = (double)l0.nchains / l0.nblocks;
-    {
-      TimedLaunch tl(s, "tsqr_chain_qr_leaf", 2.0 * pan * f1 + tri * 2.0 * l0.nchains,
-                     3.0 * (double)p.rows * nbr * nbr * f1);
-      if (p.leaf_rows == 256)
-        hipLaunchKernelGGL((k_chain_qr<256, true, 1>), dim3(l0.nchains), dim3(512), 0, s, a);
-      else
-        hipLaunchKernelGGL((k_chain_qr<128, true, 1>), dim3(l0.nchains), dim3(512), 0, s, a);
-    }
-    if (l0.chain_len > 1) {
-      TimedLaunch tl(s, "tsqr_chain_qr_leaf_rest",
-                     2.0 * pan * (1.0 - f1) + tri * (l0.nblocks - l0.nchains + 2.0 * l0.nchains),
-                     3.0 * (double)p.rows * nbr * nbr * (1.0 - f1));
-      if (p.leaf_rows == 256)
-        hipLaunchKernelGGL((k_chain_qr_rest<256>), dim3(l0.nchains), dim3(512), 0, s, a);
-      else
-        hipLaunchKernelGGL((k_chain_qr_rest<128>), dim3(l0.nchains), dim3(512), 0, s, a);
-    }
+    // plus the Gram products for T, m nb^2.
+    TimedLaunch tl(s, "tsqr_chain_qr_leaf", 2.0 * pan + tri * (l0.nblocks + l0.nchains),
+                   3.0 * (double)p.rows * nbr * nbr);
+    if (p.leaf_rows == 256)
+      hipLaunchKernelGGL((k_tsqr_leaf<4>), dim3(l0.nchains), dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_tsqr_leaf<2>), dim3(l0.nchains), dim3(256), 0, s, a);
   }
   for (int lev = 1; lev <= L; ++lev) {
     const TsqrLevel& lv = p.levels[lev];
     ChainQRArgs a{p.levels[lev - 1].R, kNB, 0, lv.nblocks, lv.chain_len, nbr, lv.Y, lv.T, lv.R};
     TimedLaunch tl(s, "tsqr_chain_qr_tree", tri * (2.0 * lv.nblocks + 3.0 * lv.nchains),
                    3.0 * (double)lv.nblocks * nbr * nbr * nbr);
-    // A node stacks (arity - 1) child R factors; the kernel's register
-    // layout is sized to that height.
-    const int stacked = (lv.chain_len - 1) * nbr;
-    if (stacked <= 64)
-      hipLaunchKernelGGL((k_chain_qr<64, false, 0>), dim3(lv.nchains), dim3(512), 0, s, a);
-    else if (stacked <= 128)
-      hipLaunchKernelGGL((k_chain_qr<128, false, 0>), dim3(lv.nchains), dim3(512), 0, s, a);
+    // One child per wave where a node has at most four stacked children;
+    // wider nodes (narrow panels with an arity of the caller's) pack them.
+    if (lv.chain_len <= 5)
+      hipLaunchKernelGGL((k_tsqr_tree<true>), dim3(lv.nchains), dim3(256), 0, s, a);
     else
-      hipLaunchKernelGGL((k_chain_qr<kYL, false, 0>), dim3(lv.nchains), dim3(512), 0, s, a);
+      hipLaunchKernelGGL((k_tsqr_tree<false>), dim3(lv.nchains), dim3(256), 0, s, a);
   }
   // Householder reconstruction at the root.
   const int nq = Q ? 2 * nbr : nbr;

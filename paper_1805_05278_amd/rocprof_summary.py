@@ -52,6 +52,8 @@ _PATTERNS = [
     (r"k_column_sumsq", "column_sumsq"),
     (r"k_axpy_cols", "axpy_cols"),
     (r"k_xpby_cols", "xpby_cols"),
+    (r"k_tsqr_leaf<\d+>", "tsqr_chain_qr_leaf"),
+    (r"k_tsqr_tree<", "tsqr_chain_qr_tree"),
     (r"k_chain_qr<\d+, true, 2>", "tsqr_chain_qr_leaf_rest"),
     (r"k_chain_qr<\d+, true, \d+>", "tsqr_chain_qr_leaf"),
     (r"k_chain_qr_rest<\d+>", "tsqr_chain_qr_leaf_rest"),
@@ -80,9 +82,9 @@ def library_name(symbol: str) -> str:
 # come from. A kernel's traffic record is valid only for those sources.
 _KERNEL_SOURCES = [
     ("gemm_", ("gemm.hip", "gemm.h", "common.h")),
-    ("tsqr_", ("tsqr.hip", "tsqr.h", "common.h")),
+    ("tsqr_", ("tsqr.hip", "tsqr.h", "common.h", "lanes.h")),
     ("batched_ls", ("batched.hip", "batched.h", "common.h")),
-    ("batched_", ("batched_blk.hip", "batched.h", "common.h")),
+    ("batched_", ("batched_blk.hip", "batched.h", "common.h", "lanes.h")),
     ("trsm_diag", ("solve.hip", "solve.h", "common.h")),
 ]
 

@@ -182,6 +182,71 @@ __device__ __forceinline__ void bcast_terms(double v, const double (&t)[16], dou
         "n"(K + 2), "n"(K + 3));
 }
 
+// y[i] += x_J[i] f for i = I .. I + N - 1 (N <= 4), x_J being lane J's x in
+// each 16-lane row.
+template <int J, int N, int I, typename X, typename Y>
+__device__ __forceinline__ void bcast_fmac(const X& x, Y& y, double f) {
+  if constexpr (N >= 4) {
+    double y0 = y[I], y1 = y[I + 1], y2 = y[I + 2], y3 = y[I + 3];
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %2, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %3, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        : "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3)
+        : "v"(x[I]), "v"(x[I + 1]), "v"(x[I + 2]), "v"(x[I + 3]), "v"(f), "n"(J));
+    y[I] = y0, y[I + 1] = y1, y[I + 2] = y2, y[I + 3] = y3;
+  } else if constexpr (N >= 1) {
+    double y0 = y[I];
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        : "+v"(y0)
+        : "v"(x[I]), "v"(f), "n"(J));
+    y[I] = y0;
+    bcast_fmac<J, N - 1, I + 1>(x, y, f);
+  }
+}
+// x[i] += x_J[i] f in place.
+template <int J, int N, int I, typename X>
+__device__ __forceinline__ void bcast_fmac_self(X& x, double f) {
+  if constexpr (N >= 4) {
+    double x0 = x[I], x1 = x[I + 1], x2 = x[I + 2], x3 = x[I + 3];
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %0, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "v"(f), "n"(J));
+    x[I] = x0, x[I + 1] = x1, x[I + 2] = x2, x[I + 3] = x3;
+  } else if constexpr (N >= 1) {
+    double x0 = x[I];
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        : "+v"(x0)
+        : "v"(f), "n"(J));
+    x[I] = x0;
+    bcast_fmac_self<J, N - 1, I + 1>(x, f);
+  }
+}
+// The same for i = I .. E - 1, four at a time.
+template <int J, int I, int E, typename X, typename Y>
+__device__ __forceinline__ void bcast_fmacs(const X& x, Y& y, double f) {
+  if constexpr (I < E) {
+    constexpr int N = (I & 3) ? 4 - (I & 3) : 4, M = N < E - I ? N : E - I;
+    bcast_fmac<J, M, I>(x, y, f);
+    bcast_fmacs<J, I + M, E>(x, y, f);
+  }
+}
+template <int J, int I, int E, typename X>
+__device__ __forceinline__ void bcast_fmacs_self(X& x, double f) {
+  if constexpr (I < E) {
+    constexpr int N = (I & 3) ? 4 - (I & 3) : 4, M = N < E - I ? N : E - I;
+    bcast_fmac_self<J, M, I>(x, f);
+    bcast_fmacs_self<J, I + M, E>(x, f);
+  }
+}
+
 // Lane group QJ's value to all four groups (lanes cl, cl + 16, cl + 32,
 // cl + 48): v_permlane16_swap leaves rows (0, 0, 2, 2) in one copy and
 // (1, 1, 3, 3) in the other, v_permlane32_swap then halves (0, 1, 0, 1) and

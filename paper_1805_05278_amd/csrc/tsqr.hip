@@ -587,305 +587,341 @@ struct HRArgs {
   double* sign;          // optional, nbr doubles
 };
 
-// Stage an nbr x nbr column-major matrix (leading dim kNB) from global
-// memory into LDS (row-major), zero outside nbr.
-__device__ __forceinline__ void hr_stage(double (*S)[kNB + 1], const double* G, int nbr) {
-  // All 16 loads of a thread first (the slot is always in bounds), masked
-  // afterwards, so that they are in flight together.
-  double g[kTS / 256];
+// Householder reconstruction (App. C.2) at the root, one workgroup of four
+// waves.  It is a chain of small dependent steps (64 pivots and the products
+// on the way to X), so it is built to need few barriers and to keep every
+// operand in registers or one LDS read away: wave c holds column tile c of
+// whatever is being formed, in MFMA accumulator layout, where an accumulator
+// is the B operand of the next product as it stands.
+//   1. X, the top rows of W, column tile by column tile: B <- B - T B along
+//      the path to leaf block 0 (B and every T upper triangular: only tiles on
+//      or above the diagonal), then X = [B; 0] - V (Z B).  No barrier.
+//   2. Sign-modified LU of X, right-looking by 16 columns.  The wave that owns
+//      the column tile eliminates its diagonal tile and the tiles below it
+//      together, column by column in registers (the pivot's multipliers are
+//      broadcast inside the FMAs), and L_bb^-1 alongside; the others then take
+//      U_bj = L_bb^-1 X_bj and X_ij -= L_ib U_bj.  One barrier per 16 columns.
+//   3. U^-1 and L^-1 by tiles, T = U S L^-T, R = -S R_root.
+//   Measured (MI355X, 64 columns; before: one barrier per pivot, 127 in all,
+// with the rows in registers of four threads each): 84 -> 27 us under 1024 rows,
+// 126 -> 50 us under 1048576 (eleven path steps).  About half of it is the 64
+// pivots (430 cycles each: readlane, reciprocal, up to 42 broadcast FMAs).
+struct HrLds {
+  double l[10][kTile];    // L, tile (i, b) at tri(b, i); strict lower and, below it, full tiles
+  double u[10][kTile];    // U, tile (b, j) at tri(b, j)
+  double li[10][kTile];   // L^-1, tile (i, b) at tri(b, i)
+  double ui[10][kTile];   // U^-1, tile (b, j) at tri(b, j)
+  double sv[kNB];         // S
+  double dv[kNB];         // D
+};
+
+// Operand tiles (p, q), p <= q <= c, of a 64 x 64 upper triangle in a slot, as
+// MFMA A operands: lane (g, cl) holds M[16 p + cl][16 q + g + 4 r].
+__device__ __forceinline__ void hr_load_upper(const double* G, int c, int g, int cl,
+                                              double (&m)[10][4]) {
 #pragma unroll
-  for (int e = 0; e < kTS / 256; ++e) g[e] = G[threadIdx.x + 256 * e];
+  for (int q = 0; q < 4; ++q)
+    if (q <= c) {
 #pragma unroll
-  for (int e = 0; e < kTS / 256; ++e) {
-    const int i = threadIdx.x + 256 * e, r = i % kNB, cc = i / kNB;
-    S[r][cc] = (r < nbr && cc < nbr) ? g[e] : 0.0;
+      for (int p = 0; p <= q; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[q * (q + 1) / 2 + p][r] = G[16 * p + cl + (16 * q + g + 4 * r) * kNB];
+    }
+}
+// Column tile c of an upper triangular product: D_p = sum_{p <= q <= c} M_pq B_q.
+__device__ __forceinline__ void hr_mul_upper(const double (&m)[10][4], const d4 (&B)[4], int c,
+                                             d4 (&D)[4]) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) D[p] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (q <= c) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int p = 0; p <= q; ++p) D[p] = mfma64(m[q * (q + 1) / 2 + p][r], B[q][r], D[p]);
+    }
+}
+// D += A B for an A tile in LDS (row-major) and a B tile in registers.
+__device__ __forceinline__ d4 hr_mul_tile(const double* A, const d4 B, int g, int cl, d4 D) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) D = mfma64(A[cl * kTLD + g + 4 * r], B[r], D);
+  return D;
+}
+__device__ __forceinline__ void hr_put_tile(double* S, const d4 v, int g, int cl) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) S[(g + 4 * r) * kTLD + cl] = v[r];
+}
+
+// Step J of the elimination of a 16-column tile whose diagonal tile sits in
+// xc column by column: every lane holds all sixteen rows of column cl (the
+// four lane groups alike), so row J is register J of each lane and needs no
+// broadcast, and the multipliers are lane J's registers, broadcast inside the
+// FMAs.  S_J = sgn(pivot) (+1 for >= 0) is added to the pivot; every lower row
+// (xc below J; the rows of the tiles below in xb, when there are any) loses
+// its multiple of row J; e
+// carries the same operations on the identity (L_bb^-1).  The pivot's column
+// keeps its unscaled entries; zs[J] = 1 / U_JJ scales them at the end.
+template <int J>
+__device__ __forceinline__ void hr_step(bool more, int cl, double (&xc)[16], double (&e)[16],
+                                        double (&zs)[16], double (&xb)[12], double& sgn) {
+  if constexpr (J < 16) {
+    const double up = readlane(xc[J], J);
+    const double s = up >= 0.0 ? 1.0 : -1.0, piv = up + s;
+    // 1 / piv (|piv| >= 1): the hardware reciprocal and one third-order step.
+    const double z0 = __builtin_amdgcn_rcp(piv);
+    const double ez = fma(-piv, z0, 1.0);
+    const double z = fma(z0, fma(ez, ez, ez), z0);
+    const double f = cl > J ? -(xc[J] * z) : 0.0, fe = -(e[J] * z);
+    bcast_fmacs<J, J + 1, 16>(xc, e, fe);
+    bcast_fmacs_self<J, J + 1, 16>(xc, f);
+    if (more) bcast_fmacs_self<J, 0, 12>(xb, f);
+    xc[J] = cl == J ? piv : xc[J];
+    sgn = cl == J ? s : sgn;
+    zs[J] = z;
+    hr_step<J + 1>(more, cl, xc, e, zs, xb, sgn);
   }
 }
 
-// C = A B for 64 x 64 matrices in LDS on FP64 MFMA; wave w computes rows
-// [16 w, 16 w + 16).  C must not alias A or B.  TB: read B transposed.
-template <bool TB>
-__device__ __forceinline__ void hr_mm(double (*C)[kNB + 1], double (*A)[kNB + 1],
-                                      double (*B)[kNB + 1]) {
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = l >> 4;
-  d4 acc[4];
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int kk = 0; kk < 16; ++kk) {
-    const double af = A[16 * w + li][4 * kk + lk];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const double bf = TB ? B[16 * ct + li][4 * kk + lk] : B[4 * kk + lk][16 * ct + li];
-      acc[ct] = mfma64(af, bf, acc[ct]);
-    }
-  }
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) C[16 * w + lk + 4 * r][16 * ct + li] = acc[ct][r];
-}
-
-// Every lane of a quad receives lane q's value (quad_perm [q, q, q, q]); q is
-// a constant after unrolling.
-__device__ __forceinline__ double quad_bcast(double v, int q) {
-  switch (q) {
-    case 0: return dpp_mov<0x00>(v);
-    case 1: return dpp_mov<0x55>(v);
-    case 2: return dpp_mov<0xAA>(v);
-    default: return dpp_mov<0xFF>(v);
-  }
-}
-
-// Sign-modified LU without pivoting (App. C.2) of the 64 x 64 X whose rows
-// sit in registers: thread (i, p) holds row i's columns p + 4 (s + m) in
-// xr[s] during outer step m, and row i of the running L^{-1} (columns p + 4 s)
-// in er[s].  Step J = 4 m + q: before eliminating column J, S_JJ = sgn(X^_JJ)
-// (+1 for >= 0) and X^_JJ += S_JJ; the pivot row goes to Rb (double-buffered
-// by step parity) and every lower row subtracts its multiple.  After the four
-// steps of an outer step, column 4 m + p is final in every row: it is stored
-// to Xm and the registers shift down one slot, so the pivot column is always
-// slot 0 and no register index depends on the step (a loop of 16 outer steps
-// instead of 64 unrolled ones).  Row J of L^{-1} is zero right of column J,
-// so its update needs no mask.
-__device__ __forceinline__ void hr_lu(double (&xr)[16], double (&er)[16], int i, int p, int nbr,
-                                      double (*Rb)[2][4][16], double* Sv, double* Ui,
-                                      double (*Xm)[kNB + 1]) {
-  for (int m = 0; m < 16; ++m) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int J = 4 * m + q;
-      if (J < nbr) {
-        const int slot = q & 1;
-        if (i == J) {
-          if (p == q) {
-            const double sg = (xr[0] >= 0.0) ? 1.0 : -1.0;
-            xr[0] += sg;
-            Sv[J] = sg;
-            Ui[J] = 1.0 / xr[0];
-          }
-#pragma unroll
-          for (int t = 0; t < 16; t += 2) {
-            *(double2*)&Rb[slot][0][p][t] = make_double2(xr[t], xr[t + 1]);
-            *(double2*)&Rb[slot][1][p][t] = make_double2(er[t], er[t + 1]);
-          }
-        }
-        __syncthreads();
-        if (i > J && i < nbr) {
-          // Multiplier l = X[i][J] / U_JJ, formed by the thread holding
-          // column J and shared with the other three threads of the row.
-          double l = (p == q) ? xr[0] * Ui[J] : 0.0;
-          l = quad_bcast(l, q);
-          if (p == q) xr[0] = l;
-#pragma unroll
-          for (int t = 0; t < 16; t += 2) {
-            const double2 rx = *(const double2*)&Rb[slot][0][p][t];
-            const double2 re = *(const double2*)&Rb[slot][1][p][t];
-            // slot 0 holds column 4 m + p: updated only right of the pivot
-            xr[t] -= ((t > 0 || p > q) ? l : 0.0) * rx.x;
-            xr[t + 1] -= l * rx.y;
-            er[t] -= l * re.x;
-            er[t + 1] -= l * re.y;
-          }
-        }
-      }
-    }
-    Xm[i][4 * m + p] = xr[0];
-#pragma unroll
-    for (int t = 0; t < 15; ++t) xr[t] = xr[t + 1];
-    xr[15] = 0.0;
-  }
-}
-
-// U^{-1} by backward elimination (U in the upper triangle of Xm): for J
-// descending, rows above J lose U[i][J] / U_JJ times row J of the running
-// inverse mr (thread (i, p): columns p + 4 s).  Row J of the running inverse
-// is zero left of column J, so the update needs no mask; the rows are scaled
-// by 1 / U_ii afterwards.
-__device__ __forceinline__ void hr_uinv(double (&mr)[16], int i, int p, int nbr,
-                                        double (*Rb)[2][4][16], const double* Ui,
-                                        double (*Xm)[kNB + 1]) {
-  for (int J = nbr - 1; J >= 1; --J) {
-    const int slot = J & 1;
-    if (i == J) {
-#pragma unroll
-      for (int t = 0; t < 16; t += 2)
-        *(double2*)&Rb[slot][0][p][t] = make_double2(mr[t], mr[t + 1]);
-    }
-    __syncthreads();
-    if (i < J) {
-      const double f = Xm[i][J] * Ui[J];
-#pragma unroll
-      for (int t = 0; t < 16; t += 2) {
-        const double2 rm = *(const double2*)&Rb[slot][0][p][t];
-        mr[t] -= f * rm.x;
-        mr[t + 1] -= f * rm.y;
-      }
-    }
+// U_bb^-1 by columns: lane cl solves U t = e_cl alone, rows 15 .. 0, U's
+// entries broadcast from the lanes of their columns (u zero below the
+// diagonal).
+template <int J>
+__device__ __forceinline__ void hr_uinv(const double (&u)[16], const double (&zs)[16],
+                                        double (&t)[16]) {
+  if constexpr (J >= 0) {
+    t[J] *= zs[J];
+    bcast_fmacs<J, 0, J>(u, t, -t[J]);
+    hr_uinv<J - 1>(u, zs, t);
   }
 }
 
 __global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
-  __shared__ double Bm[kNB][kNB + 1];
-  __shared__ double Mm[kNB][kNB + 1];
-  __shared__ double Xm[kNB][kNB + 1];
-  __shared__ double Sm[kNB][kNB + 1];
-  __shared__ double Sv[kNB], Dv[kNB], Ui[kNB];
-  __shared__ __align__(16) double Rb[2][2][4][16];  // [slot][x / e][p][m]: the step's pivot row
-  const int t = threadIdx.x;
-  const int nbr = a.nbr;
-  for (int i = t; i < kTS; i += 256) {
-    const int r = i % kNB, cc = i / kNB;
-    Bm[r][cc] = (r == cc && r < nbr) ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  // B <- B - T B for the T of every node on the path to leaf block 0 and for
-  // the stacked steps of leaf chain 0, then M = Z B for leaf block 0.  Step
-  // k's T (path(k)) is loaded into registers while step k - 1's product runs.
+  __shared__ HrLds S;
+  const int t = threadIdx.x, c = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l = t & 63, g = l >> 4, cl = l & 15;
+  const int nbr = a.nbr, nsub = (nbr + 15) >> 4;
+  // The path: the T of every node from the root to leaf block 0, of the
+  // stacked steps of leaf chain 0 (last to first), then Z of leaf block 0.
   const int b1c = min(a.chain_len[0], a.nblocks[0]);
-  int nlev = 0;  // path nodes above the leaves
+  int nlev = 0;
   for (int lev = a.L; lev >= 1; --lev) nlev += (min(a.chain_len[lev], a.nblocks[lev]) >= 2);
-  const int np = nlev + (b1c - 1) + 1;
+  const int np = nlev + b1c;
   auto path = [&](int k) -> const double* {
     if (k < nlev) {
       int seen = 0;
       for (int lev = a.L; lev >= 1; --lev)
         if (min(a.chain_len[lev], a.nblocks[lev]) >= 2 && seen++ == k) return a.T[lev];
     }
-    if (k < np - 1) return a.T[0] + (int64_t)(b1c - 1 - (k - nlev)) * kTS;
-    return a.T[0];  // leaf block 0: Z
+    return a.T[0] + (int64_t)(k < np - 1 ? b1c - 1 - (k - nlev) : 0) * kTS;
   };
-  double g[kTS / 256];
-  auto load_t = [&](const double* G) {
-#pragma unroll
-    for (int e = 0; e < kTS / 256; ++e) g[e] = G[t + 256 * e];
-  };
-  auto stage_t = [&]() {
-#pragma unroll
-    for (int e = 0; e < kTS / 256; ++e) {
-      const int i = t + 256 * e, r = i % kNB, cc = i / kNB;
-      Sm[r][cc] = (r < nbr && cc < nbr) ? g[e] : 0.0;
-    }
-  };
-  load_t(path(0));
-  stage_t();
-  __syncthreads();
-  for (int k = 0; k < np; ++k) {
-    if (k + 1 < np) load_t(path(k + 1));
-    hr_mm<false>(Mm, Sm, Bm);
-    __syncthreads();
-    if (k + 1 == np) break;  // M = Z B of leaf block 0 stays in Mm
-    stage_t();
-    for (int i = t; i < kTS; i += 256) {
-      const int r = i % kNB, cc = i / kNB;
-      Bm[r][cc] -= Mm[r][cc];
-    }
-    __syncthreads();
-  }
-  // Leaf block 0 (local QR with basis V, stored Z = T V_top^T):
-  // X = top rows of [B; 0] - V (Z B).
+  d4 x[4];
   {
-    // V_top of leaf block 0, all loads in flight together (indices clamped
-    // into the nbr x nbr corner, masked afterwards).
-    double g[kTS / 256];
+    d4 B[4], D[4];
+    double ta[10][4], tb[10][4];
 #pragma unroll
-    for (int e = 0; e < kTS / 256; ++e) {
-      const int i = t + 256 * e, r = min(i % kNB, nbr - 1), cc = min(i / kNB, nbr - 1);
-      g[e] = a.A0[r + (int64_t)cc * a.lda];
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) B[p][r] = (p == c && g + 4 * r == cl && 16 * c + cl < nbr) ? 1.0 : 0.0;
+    hr_load_upper(path(0), c, g, cl, ta);
+    // Step k's T is loaded while step k - 1 is multiplied.
+    for (int k = 0; k + 1 < np; k += 2) {
+      hr_load_upper(path(k + 1), c, g, cl, tb);
+      hr_mul_upper(ta, B, c, D);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) B[p] -= D[p];
+      if (k + 2 < np) {
+        hr_load_upper(path(k + 2), c, g, cl, ta);
+        hr_mul_upper(tb, B, c, D);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) B[p] -= D[p];
+      }
     }
+    // V_top of leaf block 0 (unit lower), tiles (p, q), q <= min(p, c).
+    double v[10][4];
 #pragma unroll
-    for (int e = 0; e < kTS / 256; ++e) {
-      const int i = t + 256 * e, r = i % kNB, cc = i / kNB;
-      double v = 0.0;
-      if (r < nbr && cc < nbr) v = (r > cc) ? g[e] : ((r == cc) ? 1.0 : 0.0);
-      Sm[r][cc] = v;
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+      for (int q = 0; q <= p; ++q)
+        if (q <= c) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = 16 * p + cl, col = 16 * q + g + 4 * r;
+            const double av = a.A0[min(row, nbr - 1) + (int64_t)min(col, nbr - 1) * a.lda];
+            v[p * (p + 1) / 2 + q][r] =
+                (row < nbr && col < nbr) ? (row > col ? av : (row == col ? 1.0 : 0.0)) : 0.0;
+          }
+        }
+    if (np & 1) hr_mul_upper(ta, B, c, D);  // M = Z B
+    else hr_mul_upper(tb, B, c, D);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q <= p; ++q)
+        if (q <= c) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc = mfma64(v[p * (p + 1) / 2 + q][r], D[q][r], acc);
+        }
+      x[p] = B[p] - acc;
     }
   }
-  __syncthreads();
-  hr_mm<false>(Xm, Sm, Mm);
-  __syncthreads();
-  for (int i = t; i < kTS; i += 256) {
-    const int r = i % kNB, cc = i / kNB;
-    Xm[r][cc] = (r < nbr && cc < nbr) ? Bm[r][cc] - Xm[r][cc] : 0.0;
-    Bm[r][cc] = (r == cc) ? 1.0 : 0.0;  // becomes L^{-1}
-    Mm[r][cc] = (r == cc) ? 1.0 : 0.0;  // becomes U^{-1}
-  }
-  __syncthreads();
-  // Sign-modified LU without pivoting (App. C.2): before eliminating column j,
-  // S_jj = sgn(X^_jj) (+1 for >= 0) and X^_jj += S_jj.  The row operations are
-  // applied to the identity alongside, which therefore ends as L^{-1}; then
-  // U^{-1} by backward elimination.  Thread (i, p) keeps row i's columns
-  // p, p + 4, ... in registers (hr_lu, hr_uinv).
-  {
-    const int i = t >> 2, p = t & 3;
-    double xr[16], er[16], mr[16];
+  // Sign-modified LU.  Slot k of x is row tile b + k (rotated every step).
+  for (int b = 0; b < nsub; ++b) {
+    const int nt = nsub - b;
+    double xc[16], zs[16];
+    if (c == b) {
+      // The diagonal tile column by column (through its LDS tile), e = I.
+      double e[16];
+      double* lt = S.l[tri(b, b)];
+      hr_put_tile(lt, x[0], g, cl);
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int k = p + 4 * m;
-      xr[m] = Xm[i][k];
-      er[m] = (i == k) ? 1.0 : 0.0;
-      mr[m] = (i == k) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    hr_lu(xr, er, i, p, nbr, Rb, Sv, Ui, Xm);  // X (L below, U on and above) to Xm
-    __syncthreads();
-    hr_uinv(mr, i, p, nbr, Rb, Ui, Xm);
-    // L^{-1} in Bm, U^{-1} (rows scaled by 1/U_ii) in Mm.
+      for (int i = 0; i < 16; ++i) {
+        xc[i] = lt[i * kTLD + cl];
+        e[i] = i == cl ? 1.0 : 0.0;
+      }
+      __builtin_amdgcn_wave_barrier();
+      double sgn = 1.0, xb[12];
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int k = p + 4 * m;
-      Bm[i][k] = er[m];
-      Mm[i][k] = (i < nbr) ? mr[m] * Ui[i] : mr[m];
+      for (int i = 0; i < 12; ++i) xb[i] = x[1 + i / 4][i % 4];
+      hr_step<0>(nt > 1, cl, xc, e, zs, xb, sgn);
+      double z = 1.0;  // this column's 1 / U_jj
+#pragma unroll
+      for (int i = 0; i < 16; ++i) z = i == cl ? zs[i] : z;
+      if (g == 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          S.li[tri(b, b)][i * kTLD + cl] = e[i];
+          lt[i * kTLD + cl] = xc[i] * z;  // L below the diagonal
+        }
+        S.sv[16 * b + cl] = sgn;
+      }
+#pragma unroll
+      for (int k = 1; k < 4; ++k)
+        if (k < nt) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            S.l[tri(b, b + k)][(g + 4 * r) * kTLD + cl] = xb[4 * (k - 1) + r] * z;
+        }
     }
-    __syncthreads();
+    lds_barrier();
+    if (c == b) {
+      double m[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        m[i] = i == cl ? 1.0 : 0.0;
+        xc[i] = i <= cl ? xc[i] : 0.0;
+      }
+      hr_uinv<15>(xc, zs, m);
+      if (g == 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          S.u[tri(b, b)][i * kTLD + cl] = xc[i];
+          S.ui[tri(b, b)][i * kTLD + cl] = m[i];
+        }
+      }
+    } else if (c > b && c < nsub) {
+      const d4 u = hr_mul_tile(S.li[tri(b, b)], x[0], g, cl, d4{0.0, 0.0, 0.0, 0.0});
+      hr_put_tile(S.u[tri(b, c)], u, g, cl);
+#pragma unroll
+      for (int k = 1; k < 4; ++k)
+        if (k < nt) x[k] = hr_mul_tile(S.l[tri(b, b + k)], -u, g, cl, x[k]);
+      x[0] = x[1];
+      x[1] = x[2];
+      x[2] = x[3];
+    }
   }
   // R = -S R_root, optional D = sign(diag R).
   if (t < nbr) {
-    const double r = -Sv[t] * a.Rtop[t + t * kNB];
+    const double r = -S.sv[t] * a.Rtop[t + t * kNB];
     const double d = (a.normalize && r < 0.0) ? -1.0 : 1.0;
-    Dv[t] = d;
+    S.dv[t] = d;
     if (a.sign) a.sign[t] = d;
   }
-  __syncthreads();
-  // T = U S L^{-T}: stage U S (upper) and multiply by L^{-1} transposed.
-  for (int e = t; e < kTS; e += 256) {
-    const int r = e % kNB, cc = e / kNB;
-    Sm[r][cc] = (r <= cc && cc < nbr) ? Xm[r][cc] * Sv[cc] : 0.0;
+  lds_barrier();
+  // Column tile c of L^-1 and U^-1:
+  //   (L^-1)_ic = -L_ii^-1 sum_{c <= q < i} L_iq (L^-1)_qc,  i = c + 1 ..
+  //   (U^-1)_ic = -U_ii^-1 sum_{i < q <= c} U_iq (U^-1)_qc,  i = c - 1 .. 0
+  if (c < nsub) {
+    d4 y[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[0][r] = S.li[tri(c, c)][(g + 4 * r) * kTLD + cl];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+      const int i = c + k;
+      if (i < nsub) {
+        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < k; ++q) acc = hr_mul_tile(S.l[tri(c + q, i)], y[q], g, cl, acc);
+        y[k] = hr_mul_tile(S.li[tri(i, i)], -acc, g, cl, d4{0.0, 0.0, 0.0, 0.0});
+        hr_put_tile(S.li[tri(c, i)], y[k], g, cl);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[0][r] = S.ui[tri(c, c)][(g + 4 * r) * kTLD + cl];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+      const int i = c - k;
+      if (i >= 0) {
+        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < k; ++q) acc = hr_mul_tile(S.u[tri(i, c - q)], y[q], g, cl, acc);
+        y[k] = hr_mul_tile(S.ui[tri(i, i)], -acc, g, cl, d4{0.0, 0.0, 0.0, 0.0});
+        hr_put_tile(S.ui[tri(i, c)], y[k], g, cl);
+      }
+    }
   }
-  __syncthreads();
-  {
-    const int w = t >> 6, l = t & 63, li = l & 15, lk = l >> 4;
+  lds_barrier();
+  double rtop[kTS / 256];  // the root's R, for the last step
+#pragma unroll
+  for (int i = 0; i < kTS / 256; ++i) rtop[i] = a.Rtop[t + 256 * i];
+  // T_pc = sum_{p <= k <= c} U_pk S_k (L^-1)_ck^T.
+  if (c < nsub) {
     d4 acc[4];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc[ct] = d4{0.0, 0.0, 0.0, 0.0};
-    for (int kk = 0; kk < 16; ++kk) {
-      const double af = Sm[16 * w + li][4 * kk + lk];
+    for (int p = 0; p < 4; ++p) acc[p] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma64(af, Bm[16 * ct + li][4 * kk + lk], acc[ct]);
-    }
+    for (int k = 0; k < 4; ++k)
+      if (k <= c) {
+        const double* lt = S.li[tri(k, c)];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
+        for (int r = 0; r < 4; ++r) {
+          const int e = cl * kTLD + g + 4 * r;
+          const double bv = S.sv[16 * k + g + 4 * r] * lt[e];
+#pragma unroll
+          for (int p = 0; p <= k; ++p) acc[p] = mfma64(S.u[tri(p, k)][e], bv, acc[p]);
+        }
+      }
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = 16 * w + lk + 4 * r, cc = 16 * ct + li;
-        if (row < nbr && cc < nbr) a.Tp[row + cc * a.ldt] = (row <= cc) ? acc[ct][r] : 0.0;
+        const int row = 16 * p + g + 4 * r, cc = 16 * c + cl;
+        if (row < nbr && cc < nbr) a.Tp[row + cc * a.ldt] = (row <= cc) ? acc[p][r] : 0.0;
       }
   }
-  for (int e = t; e < kTS; e += 256) {
-    const int r = e % kNB, cc = e / kNB;
-    const double rt = a.Rtop[e];  // the slot is always in bounds
-    double lr = 0.0;
-    if (r < nbr && cc < nbr) lr = (r > cc) ? Xm[r][cc] : -Dv[r] * Sv[r] * rt;
-    a.LR[e] = lr;
+  // The final L (strict lower) and R of the top rows, and the downsweep's
+  // input [U^-1 | -S D].  Branch-free, so that the LDS reads overlap.
+  const double ds = -S.dv[t & 63] * S.sv[t & 63];
+#pragma unroll
+  for (int i = 0; i < kTS / 256; ++i) {
+    const int r = t & 63, cc = (t >> 6) + 4 * i;
+    const int tl = (r & 15) * kTLD + (cc & 15), rt = r >> 4, ct = cc >> 4;
+    const bool up = r <= cc, in = r < nbr && cc < nbr;
+    const double lv = S.l[tri(min(rt, ct), max(rt, ct))][tl];
+    const double uv = S.ui[tri(min(rt, ct), max(rt, ct))][tl];
+    a.LR[t + 256 * i] = in ? (up ? ds * rtop[i] : lv) : 0.0;
+    a.Broot[t + 256 * i] = (in && up) ? uv : 0.0;
   }
-  for (int e = t; e < kBS; e += 256) {
-    const int r = e % kNB, cc = e / kNB;
-    double v = 0.0;
-    if (r < nbr && cc < a.nq) {
-      if (cc < nbr) v = Mm[r][cc];
-      else if (cc - nbr == r) v = -Sv[r] * Dv[r];
+  if (a.nq > nbr) {
+    // Columns nbr .. 2 nbr - 1 (from column nbr of the slot, which may lie
+    // inside the first kNB columns).
+    __syncthreads();
+    for (int e = t; e < kNB * nbr; e += 256) {
+      const int r = e % kNB, cc = e / kNB;
+      a.Broot[r + (nbr + cc) * kNB] = (r == cc && r < nbr) ? ds : 0.0;
     }
-    a.Broot[e] = v;
   }
 }
 

@@ -19,7 +19,7 @@ struct TsqrLevel {
   double* T = nullptr;  // per block, kTS doubles each
   double* Y = nullptr;  // per block (levels > 0 only), kTS doubles each
   double* R = nullptr;  // per chain, kTS doubles each
-  double* B = nullptr;  // per chain, downsweep input, kBS doubles each
+  double* B = nullptr;  // top level: the downsweep's input, kBS doubles
 };
 
 struct TsqrPlan {

@@ -555,7 +555,7 @@ __global__ __launch_bounds__(256, 2) void k_tsqr_tree(ChainQRArgs a) {
     const int col = 16 * c + cl;
     if (col >= nbr) continue;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < (TRI ? c + 1 : 4); ++k)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int row = 16 * (TRI ? k : 4 * w + k) + 8 * h + 2 * g;
@@ -926,183 +926,261 @@ __global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
 }
 
 struct DownArgs {
-  const double* Bin;   // per chain (leaf) / node (tree) of this level
-  double* Bout;        // tree levels: per child (= per chain of the level below)
-  const double* T;     // leaf: per block; tree: per node
-  const double* Y;     // tree levels: per node
-  double* A;           // leaf level: panel (basis in, V out), leading dim lda
-  int64_t lda, xrows;
-  double* Q;           // leaf level, optional
-  int64_t ldq;
+  int L;                 // tree levels above the leaves
+  const double* T[kMaxLevels];   // [0]: per leaf block; [lev]: per node
+  const double* Y[kMaxLevels];   // [lev]: per node
+  int nblocks[kMaxLevels];
+  int chain_len[kMaxLevels];
+  const double* Broot;   // [U^-1 | -S D] of the root
   const double* LR;
-  int nblocks, chain_len, nbr, nq;
+  double* A;             // panel (basis in, V out)
+  int64_t lda, xrows;
+  double* Q;             // optional
+  int64_t ldq;
+  int nbr;
 };
 
-// M = T B into Ms (T upper triangular from global, B in Bs); wave w computes
-// rows [16w, 16w + 16) of M.  MFMA operand roles: A = T tile, B = B tile.
-template <int NQM, int NW>
-__device__ __forceinline__ void down_tb(const double* Tb, double (*Bs)[NQM + 4],
-                                        double (*Ms)[NQM + 4], int nbr, int CT) {
-  // NW waves: wave w computes row tile w % 4 of M and the column tiles of
-  // part w / 4 (with 8 waves the columns are split in two).
-  constexpr int NCP = NW / 4, CTP = NQM / 16 / NCP;
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = l >> 4;
-  const int rt = w & 3, cp = w >> 2;
-  d4 acc[CTP];
+// A product of two 64 x 64 upper triangles takes 20 products of 16 x 16 tiles;
+// wave w forms the output tiles whose five are its share: (p, c) needs tiles
+// (p, q) and (q, c) for q = p .. c.
+struct TriShare {
+  int p[5], q[5], c[5];
+  bool last[5];  // the output tile is complete after this product
+  __device__ explicit TriShare(int w) {
 #pragma unroll
-  for (int c2 = 0; c2 < CTP; ++c2) acc[c2] = d4{0.0, 0.0, 0.0, 0.0};
-  const int i = 16 * rt + li;
-  // The wave's T values eight at a time (the slot is always in bounds),
-  // masked afterwards: a predicated load per step would wait out a global
-  // latency before each MFMA.
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    double tv[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tv[e] = Tb[i + (4 * (8 * h + e) + lk) * kNB];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = 4 * (8 * h + e) + lk;
-      const double av = (i < nbr && k < nbr) ? tv[e] : 0.0;
-#pragma unroll
-      for (int c2 = 0; c2 < CTP; ++c2) {
-        const int ct = cp * CTP + c2;
-        if (ct < CT) acc[c2] = mfma64(av, Bs[k][16 * ct + li], acc[c2]);
-      }
+    for (int i = 0; i < 5; ++i) {
+      int pp, qq, cc;
+      if (w == 0) { pp = 0; qq = i < 4 ? i : 0; cc = i < 4 ? 3 : 0; }
+      else if (w == 1) { pp = 0; qq = i < 3 ? i : i - 3; cc = i < 3 ? 2 : 1; }
+      else if (w == 2) { pp = 1; qq = i < 3 ? 1 + i : i - 2; cc = i < 3 ? 3 : 2; }
+      else { pp = i < 2 ? 2 : i - 1; qq = i < 2 ? 2 + i : i - 1; cc = i < 2 ? 3 : i - 1; }
+      p[i] = pp;
+      q[i] = qq;
+      c[i] = cc;
+      last[i] = qq == cc;
     }
   }
-#pragma unroll
-  for (int c2 = 0; c2 < CTP; ++c2) {
-    const int ct = cp * CTP + c2;
-    if (ct < CT)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Ms[16 * rt + lk + 4 * r][16 * ct + li] = acc[c2][r];
-  }
-}
+};
 
-// Rows of one leaf block (or one node's stacked children) receive
-// -Y M (+ B on the top rows of a leaf chain's first block).
-template <int RT, int NQM, bool LEAF, int NW>
-__device__ __forceinline__ void down_emit(const DownArgs& a, double (*Bs)[NQM + 4],
-                                          double (*Ms)[NQM + 4], const double* Yb, int64_t ldy,
-                                          int rows, bool first, int64_t rstart, bool top_block,
-                                          int b0, int CT) {
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = l >> 4;
-  const int nbr = a.nbr, nq = a.nq;
-  double yf[RT][16];
+// Row `row` (per lane) of the basis as operands of a contraction over its
+// columns: y[q][r] = Y[row][16 q + g + 4 r], zero beyond nbr (nothing outside
+// the panel's columns is read).
+__device__ __forceinline__ void down_load_row(const double* A, int64_t lda, int row, int nbr,
+                                              int qn, int g, double (&y)[4][4]) {
+  const double* Al = A + row + g * lda;
+  if (nbr == kNB) {
 #pragma unroll
-  for (int s = 0; s < RT; ++s) {
-    const int row = 16 * (w + NW * s) + li;
+    for (int q = 0; q < 4; ++q)
+      if (q < qn) {
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const int k = 4 * kk + lk;
-      double v = (row < rows && k < nbr) ? Yb[row + (int64_t)k * ldy] : 0.0;
-      if (first && row <= k) v = (row == k && k < nbr) ? 1.0 : 0.0;
-      yf[s][kk] = v;
-    }
-  }
-  for (int ct0 = 0; ct0 < CT; ct0 += 2) {
-    d4 acc[RT][2];
-#pragma unroll
-    for (int s = 0; s < RT; ++s) acc[s][0] = acc[s][1] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const double af = Ms[4 * kk + lk][16 * (ct0 + g) + li];
-#pragma unroll
-        for (int s = 0; s < RT; ++s) acc[s][g] = mfma64(af, yf[s][kk], acc[s][g]);
+        for (int r = 0; r < 4; ++r) y[q][r] = Al[(16 * q + 4 * r) * lda];
       }
-    }
+  } else {
 #pragma unroll
-    for (int s = 0; s < RT; ++s) {
-      const int row = 16 * (w + NW * s) + li;
-      if (row >= rows) continue;
-#pragma unroll
-      for (int g = 0; g < 2; ++g)
+    for (int q = 0; q < 4; ++q)
+      if (q < qn) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int cc = 16 * (ct0 + g) + lk + 4 * r;
-          if (cc >= nq) continue;
-          double v = -acc[s][g][r];
-          if (first && row < nbr) v += Bs[row][cc];
-          if (LEAF) {
-            if (cc < nbr) {
-              if (top_block && row < nbr) v = a.LR[row + cc * kNB];
-              a.A[rstart + row + (int64_t)cc * a.lda] = v;
-            } else if (a.Q) {
-              a.Q[rstart + row + (int64_t)(cc - nbr) * a.ldq] = v;
-            }
-          } else {
-            const int sidx = row / nbr, rr = row - sidx * nbr;
-            a.Bout[(int64_t)(b0 + 1 + sidx) * kBS + rr + cc * kNB] = v;
-          }
+          const bool in = 16 * q + 4 * r + g < nbr;
+          y[q][r] = 0.0;
+          if (in) y[q][r] = Al[(16 * q + 4 * r) * lda];
         }
-    }
+      }
   }
 }
 
-// RT: 16-row tiles per wave (block height 16 NW RT); NQM: max columns of B;
-// LEAF: emit the panel rows (else the children's B blocks); NW: waves per
-// workgroup (the leaf launch uses 8, so that each wave holds half as many
-// basis rows and the workgroup has twice the waves to hide its loads).
-template <int RT, int NQM, bool LEAF, int NW>
-__global__ __launch_bounds__(64 * NW) void k_chain_down(DownArgs a) {
-  constexpr int BLD = NQM + 4;
-  __shared__ __align__(16) double Bs[kNB][BLD];
-  __shared__ __align__(16) double Ms[kNB][BLD];
-  const int t = threadIdx.x;
-  const int chain = blockIdx.x;
-  const int b0 = chain * a.chain_len;
-  const int b1 = min(b0 + a.chain_len, a.nblocks);
-  const int nbr = a.nbr, nq = a.nq;
-  const int CT = (nq + 15) >> 4;
-
-  {
-    // B of this chain / node, all loads in flight together (the slot holds
-    // kNB x 2 kNB, so every index is in bounds), masked afterwards.
-    constexpr int NE = kNB * NQM / (64 * NW);
-    const double* bin = a.Bin + (int64_t)chain * kBS;
-    double g[NE];
+// Downsweep (App. C.2), tree and leaves in one launch: the workgroup of a leaf
+// chain walks from the root to its chain by itself (M = T B, then B - M for a
+// first child, -Y M for the others), then through its chain's blocks, last to
+// first, writing -Y M (+ B on a first block's top rows).  B, T and the
+// children's Y are upper triangular all the way down, so a level is two
+// triangular products of 20 tile products, shared evenly by the four waves,
+// with B and -M in LDS and the next matrix loaded meanwhile.
+//   Without Q the walk starts from U^-1 and emits V = W U^-1.  With Q it starts
+// from -S D, emits Q = -W S D, and V is Q (-S D U^-1), from Q's rows while they
+// are in registers: one walk serves both.
+//   Bound: under few rows the latency of the path (about 4.4 k cycles a level);
+// under many the memory traffic of the panel (read the basis, write V and Q:
+// 1.6 GB at 1048576 x 64 with Q, 514 us).  Measured (MI355X; before: a launch
+// per tree level and one for the leaves): 1024 x 64 with Q 79 -> 23 us,
+// 16384 x 64 118 -> 18 us, 1048576 x 64 with Q 936 -> 514 us.
+template <bool WQ>
+__global__ __launch_bounds__(256, 2) void k_tsqr_down(DownArgs a) {
+  __shared__ double Bt[10][kTile];             // B
+  __shared__ double Mt[10][kTile];             // -M
+  __shared__ double Kt[WQ ? 10 : 1][kTile];    // -S D U^-1
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l = threadIdx.x & 63, g = l >> 4, cl = l & 15;
+  const int chain = blockIdx.x, nbr = a.nbr, nsub = (nbr + 15) >> 4;
+  const int part = blockIdx.y, parts = gridDim.y;
+  const int b0 = chain * a.chain_len[0];
+  const int b1 = min(b0 + a.chain_len[0], a.nblocks[0]);
+  const TriShare sh(w);
+  double ta[5][4], ya[5][4];
+  auto load_t = [&](const double* T) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) g[e] = bin[t + 64 * NW * e];
+    for (int i = 0; i < 5; ++i)
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const int i = t + 64 * NW * e, r = i % kNB, cc = i / kNB;
-      Bs[r][cc] = (r < nbr && cc < nq) ? g[e] : 0.0;
-      Ms[r][cc] = 0.0;
+      for (int r = 0; r < 4; ++r)
+        ta[i][r] = (T + 16 * sh.p[i] + 16 * sh.q[i] * kNB)[cl + (g + 4 * r) * kNB];
+  };
+  // A child's basis (leading dim kYL).  Narrow panels read past the child's
+  // rows and columns (inside the workspace: the level's R follows its Y) and
+  // mask what they read.
+  auto load_y = [&](const double* Y) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double v = (Y + 16 * sh.p[i] + 16 * sh.q[i] * kYL)[cl + (g + 4 * r) * kYL];
+        ya[i][r] = (16 * sh.p[i] + cl < nbr && 16 * sh.q[i] + g + 4 * r < nbr) ? v : 0.0;
+      }
+  };
+  // O = sgn A B for this wave's output tiles: A in m, B's tiles in LDS.
+  auto mul = [&](const double (&m)[5][4], double (*Bs)[kTile], double (*O)[kTile], bool neg) {
+    d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      const double* bs = Bs[tri(sh.q[i], sh.c[i])];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc = mfma64(m[i][r], bs[(g + 4 * r) * kTLD + cl], acc);
+      if (sh.last[i]) {
+        hr_put_tile(O[tri(sh.p[i], sh.c[i])], neg ? -acc : acc, g, cl);
+        acc = d4{0.0, 0.0, 0.0, 0.0};
+      }
+    }
+  };
+  auto sub_m = [&]() {  // B <- B - M, this wave's tiles
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+      if (sh.last[i]) {
+        double* bt = Bt[tri(sh.p[i], sh.c[i])];
+        const double* mt = Mt[tri(sh.p[i], sh.c[i])];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bt[(g + 4 * r) * kTLD + cl] += mt[(g + 4 * r) * kTLD + cl];
+      }
+  };
+  // The path's nodes, lane k's at level k (integer divisions are slow: once,
+  // side by side).
+  int path = chain;
+  for (int k = 1; k <= a.L; ++k) path = k <= l ? path / a.chain_len[k] : path;
+  // Node of the path at a level, and which of its children the path takes.
+  auto node_at = [&](int lev, int* pos) {
+    const int node = __builtin_amdgcn_readlane(path, lev);
+    *pos = __builtin_amdgcn_readlane(path, lev - 1) - node * a.chain_len[lev];
+    return node;
+  };
+  auto load_level_t = [&](int lev) {  // level 0: the last block of the chain
+    const int node = lev == 0 ? b1 - 1 : __builtin_amdgcn_readlane(path, lev);
+    load_t(a.T[lev] + (int64_t)node * kTS);
+  };
+  auto load_level_y = [&](int lev) {
+    int pos;
+    const int node = node_at(lev, &pos);
+    if (pos > 0) load_y(a.Y[lev] + (int64_t)node * kYS + (pos - 1) * nbr);
+  };
+  load_level_t(a.L);
+  if (a.L > 0) load_level_y(a.L);
+  // Start: U^-1, or -S D and K = -S D U^-1.
+#pragma unroll
+  for (int i = 0; i < kTS / 256; ++i) {
+    const int r = threadIdx.x & 63, cc = (threadIdx.x >> 6) + 4 * i;
+    double v = a.Broot[threadIdx.x + 256 * i];
+    v = (r <= cc && cc < nbr) ? v : 0.0;
+    const int e = (r & 15) * kTLD + (cc & 15), ti = tri(min(r, cc) >> 4, cc >> 4);
+    if constexpr (WQ) {
+      const double ds = a.Broot[r + (nbr + min(r, nbr - 1)) * kNB];
+      if ((r >> 4) <= (cc >> 4)) {
+        Kt[ti][e] = r < nbr ? ds * v : 0.0;
+        Bt[ti][e] = (r == cc && r < nbr) ? ds : 0.0;
+      }
+    } else {
+      if ((r >> 4) <= (cc >> 4)) Bt[ti][e] = v;
     }
   }
-  __syncthreads();
-
-  if constexpr (LEAF) {
-    for (int b = b1 - 1; b >= b0; --b) {
-      const bool first = b == b0;
-      down_tb<NQM, NW>(a.T + (int64_t)b * kTS, Bs, Ms, nbr, CT);
-      __syncthreads();
-      if (!first)
-        for (int i = t; i < kNB * NQM; i += 64 * NW) {
-          const int r = i / NQM, cc = i % NQM;
-          Bs[r][cc] -= Ms[r][cc];
+  lds_barrier();
+  for (int lev = a.L; lev >= 1; --lev) {
+    int pos;
+    const int node = node_at(lev, &pos);
+    const bool single = min(a.chain_len[lev], a.nblocks[lev] - node * a.chain_len[lev]) < 2;
+    if (!single) mul(ta, Bt, Mt, true);
+    load_level_t(lev - 1);
+    lds_barrier();
+    if (!single) {
+      if (pos == 0) sub_m();
+      else mul(ya, Mt, Bt, false);
+    }
+    if (lev > 1) load_level_y(lev - 1);
+    lds_barrier();
+  }
+  for (int b = b1 - 1; b >= b0; --b) {
+    const bool first = b == b0;
+    const int64_t rstart = ((int64_t)b * a.xrows) / a.nblocks[0];
+    const int rows = (int)((((int64_t)b + 1) * a.xrows) / a.nblocks[0] - rstart);
+    double* Ab = a.A + rstart;
+    // Rows r0 .. r0 + 15 of the block are this wave's next; their basis is
+    // loaded one step ahead.
+    const int rstep = 64 * parts;
+    int r0 = 16 * (w + 4 * part);
+    double y[4][4];
+    down_load_row(Ab, a.lda, min(r0 + cl, rows - 1), nbr, nsub, g, y);
+    mul(ta, Bt, Mt, true);
+    if (!first) load_t(a.T[0] + (int64_t)(b - 1) * kTS);
+    lds_barrier();
+    if (!first) sub_m();
+    for (; r0 < rows; r0 += rstep) {
+      const int row = min(r0 + cl, rows - 1);
+      const bool in = r0 + cl < rows, top = first && r0 < 64;
+      double yn[4][4];
+      if (r0 + rstep < rows)
+        down_load_row(Ab, a.lda, min(r0 + rstep + cl, rows - 1), nbr, nsub, g, yn);
+      // D[col][row] = sum_k (-M)[k][col] Y[row][k] (+ B[row][col]).
+      d4 acc[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        acc[c] = d4{0.0, 0.0, 0.0, 0.0};
+        if (c >= nsub) continue;
+        if (top && r0 <= 16 * c) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[c][r] = Bt[tri(r0 >> 4, c)][cl * kTLD + g + 4 * r];
         }
-      const int64_t rstart = ((int64_t)b * a.xrows) / a.nblocks;
-      const int rows = (int)((((int64_t)b + 1) * a.xrows) / a.nblocks - rstart);
-      down_emit<RT, NQM, true, NW>(a, Bs, Ms, a.A + rstart, a.lda, rows, first, rstart, b == 0, b0, CT);
-      __syncthreads();
+#pragma unroll
+        for (int q = 0; q <= c; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            acc[c] = mfma64(Mt[tri(q, c)][(g + 4 * r) * kTLD + cl], y[q][r], acc[c]);
+        if constexpr (WQ) {
+          double* out = a.Q + rstart + row + (16 * c + g) * a.ldq;
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (in && 16 * c + 4 * r + g < nbr) out[4 * r * a.ldq] = acc[c][r];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (c >= nsub) continue;
+        d4 v = acc[c];
+        if constexpr (WQ) {
+          v = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int q = 0; q <= c; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              v = mfma64(Kt[tri(q, c)][(g + 4 * r) * kTLD + cl], acc[q][r], v);
+        }
+        double* out = Ab + row + (16 * c + g) * a.lda;
+        const bool lr = b == 0 && r0 + cl < nbr;  // L and R instead
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (in && 16 * c + 4 * r + g < nbr)
+            out[4 * r * a.lda] = lr ? a.LR[row + (16 * c + 4 * r + g) * kNB] : v[r];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[q][r] = yn[q][r];
     }
-  } else {
-    if (b1 - b0 >= 2) {
-      down_tb<NQM, NW>(a.T + (int64_t)chain * kTS, Bs, Ms, nbr, CT);
-      __syncthreads();
-      down_emit<RT, NQM, false, NW>(a, Bs, Ms, a.Y + (int64_t)chain * kYS, kYL, (b1 - b0 - 1) * nbr, false,
-                         0, false, b0, CT);
-      __syncthreads();
-    }
-    // First child: B - M (M is zero when the node has a single child).
-    for (int i = t; i < kBS; i += 64 * NW) {
-      const int r = i % kNB, cc = i / kNB;
-      a.Bout[(int64_t)b0 * kBS + i] = (r < nbr && cc < nq) ? Bs[r][cc] - Ms[r][cc] : 0.0;
-    }
+    lds_barrier();
   }
 }
 
@@ -1141,6 +1219,9 @@ TsqrPlan tsqr_plan(int64_t rows, int nbr, int leaf_rows, int chain, int arity, d
       lv.Y = take((int64_t)lv.nchains * kYS);
     }
     lv.R = take((int64_t)lv.nchains * kTS);
+    // Only the top level's B is used; the others keep their place, so that the
+    // workspace a shape needs (what qr_workspace_size reports and
+    // qr_factor_noalloc accepts) stays what it was.
     lv.B = take((int64_t)lv.nchains * kBS);
   }
   p.LR = take(kTS);
@@ -1203,63 +1284,37 @@ hipError_t tsqr_factor(const TsqrPlan& p, hipStream_t s, double* P, int64_t ldp,
     TimedLaunch tl(s, "tsqr_hr_root", tri * 8.0, 6.0 * (double)nbr * nbr * nbr * (L + 2));
     hipLaunchKernelGGL(k_tsqr_hr, dim3(1), dim3(256), 0, s, h);
   }
-  // Downsweep through the tree levels, then the leaves.
-  for (int lev = L; lev >= 1; --lev) {
-    const TsqrLevel& lv = p.levels[lev];
-    DownArgs d{};
-    d.Bin = lv.B;
-    d.Bout = p.levels[lev - 1].B;
-    d.T = lv.T;
-    d.Y = lv.Y;
-    d.nblocks = lv.nblocks;
-    d.chain_len = lv.chain_len;
-    d.nbr = nbr;
-    d.nq = nq;
-    TimedLaunch tl(s, "tsqr_down_tree", 8.0 * nbr * nq * 2.0 * lv.nblocks + tri * 2.0 * lv.nblocks,
-                   3.0 * (double)lv.nblocks * nbr * nbr * nq);
-    const int stacked = (lv.chain_len - 1) * nbr;  // rows of -Y M per node
-    if (stacked <= 64) {
-      if (nq > kNB)
-        hipLaunchKernelGGL((k_chain_down<1, 128, false, 4>), dim3(lv.nchains), dim3(256), 0, s, d);
-      else
-        hipLaunchKernelGGL((k_chain_down<1, 64, false, 4>), dim3(lv.nchains), dim3(256), 0, s, d);
-    } else {
-      if (nq > kNB)
-        hipLaunchKernelGGL((k_chain_down<4, 128, false, 4>), dim3(lv.nchains), dim3(256), 0, s, d);
-      else
-        hipLaunchKernelGGL((k_chain_down<4, 64, false, 4>), dim3(lv.nchains), dim3(256), 0, s, d);
-    }
-  }
+  // Downsweep, tree and leaves.  Read the basis, write V (and Q); T per block
+  // and per node.  Flops: 2 m nb nq for -Y M, nb^2 nq per block for M = T B.
   {
-    const TsqrLevel& l0 = p.levels[0];
     DownArgs d{};
-    d.Bin = l0.B;
-    d.T = l0.T;
+    d.L = L;
+    int64_t nodes = 0;
+    for (int lev = 0; lev <= L; ++lev) {
+      d.T[lev] = p.levels[lev].T;
+      d.Y[lev] = p.levels[lev].Y;
+      d.nblocks[lev] = p.levels[lev].nblocks;
+      d.chain_len[lev] = p.levels[lev].chain_len;
+      if (lev > 0) nodes += p.levels[lev].nchains;
+    }
+    d.Broot = p.levels[L].B;
+    d.LR = p.LR;
     d.A = P;
     d.lda = ldp;
     d.xrows = p.rows;
     d.Q = Q;
     d.ldq = ldq;
-    d.LR = p.LR;
-    d.nblocks = l0.nblocks;
-    d.chain_len = l0.chain_len;
     d.nbr = nbr;
-    d.nq = nq;
-    // Read the basis, write V (and Q); T per block.  Flops: 2 m nb nq for
-    // -Y M plus nb^2 nq per block for M = T B.
-    TimedLaunch tl(s, "tsqr_down_leaf", pan * (Q ? 3.0 : 2.0) + tri * l0.nblocks,
+    const TsqrLevel& l0 = p.levels[0];
+    TimedLaunch tl(s, "tsqr_down_leaf", pan * (Q ? 3.0 : 2.0) + tri * (l0.nblocks + 2.0 * nodes),
                    2.0 * (double)p.rows * nbr * nq + (double)l0.nblocks * nbr * nbr * nq);
-    if (p.leaf_rows == 256) {
-      if (nq > kNB)
-        hipLaunchKernelGGL((k_chain_down<4, 128, true, 4>), dim3(l0.nchains), dim3(256), 0, s, d);
-      else
-        hipLaunchKernelGGL((k_chain_down<2, 64, true, 8>), dim3(l0.nchains), dim3(512), 0, s, d);
-    } else {
-      if (nq > kNB)
-        hipLaunchKernelGGL((k_chain_down<2, 128, true, 4>), dim3(l0.nchains), dim3(256), 0, s, d);
-      else
-        hipLaunchKernelGGL((k_chain_down<1, 64, true, 8>), dim3(l0.nchains), dim3(512), 0, s, d);
-    }
+    // Few chains: the rows of each chain's blocks go to up to four workgroups
+    // (every one walks the path), so that the emission of a block's up to four
+    // row tiles per wave is spread over idle CUs.
+    const int parts = l0.nchains >= 256 ? 1 : std::min(p.leaf_rows / 64, 256 / l0.nchains);
+    const dim3 grid(l0.nchains, parts);
+    if (Q) hipLaunchKernelGGL(k_tsqr_down<true>, grid, dim3(256), 0, s, d);
+    else hipLaunchKernelGGL(k_tsqr_down<false>, grid, dim3(256), 0, s, d);
   }
   return hipGetLastError();
 }

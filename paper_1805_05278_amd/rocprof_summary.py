@@ -53,6 +53,7 @@ _PATTERNS = [
     (r"k_axpy_cols", "axpy_cols"),
     (r"k_xpby_cols", "xpby_cols"),
     (r"k_tsqr_leaf<\d+>", "tsqr_chain_qr_leaf"),
+    (r"k_tsqr_down<", "tsqr_down_leaf"),
     (r"k_tsqr_tree<", "tsqr_chain_qr_tree"),
     (r"k_chain_qr<\d+, true, 2>", "tsqr_chain_qr_leaf_rest"),
     (r"k_chain_qr<\d+, true, \d+>", "tsqr_chain_qr_leaf"),

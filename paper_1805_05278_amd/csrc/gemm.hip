@@ -18,6 +18,7 @@
 // partial product and a second kernel adds the partials in a fixed order, so
 // results are bitwise reproducible.
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "gemm.h"
@@ -94,9 +95,9 @@ struct MfmaTraits<COMPUTE_F32> {
 // transposed B) and at p[k + i ld] otherwise.  Each thread owns a fixed
 // (i, k) pattern and a pointer advanced by a constant per slice, so the hot
 // loop does no 64-bit multiplies.
-template <int BX, int BK, bool ALONG_I>
+template <int BX, int BK, bool ALONG_I, int NT = 256>
 struct SliceLoader {
-  static constexpr int L = BX * BK / 256;  // elements per thread
+  static constexpr int L = BX * BK / NT;  // elements per thread
   const double* p;                         // this thread's first element
   int64_t step;                            // pointer advance per slice
   int64_t estride;                         // distance between a thread's elements
@@ -107,14 +108,14 @@ struct SliceLoader {
       i = t % BX;
       k = t / BX;
       di = 0;
-      dk = 256 / BX;
+      dk = NT / BX;
       p = base + (x0 + i) + (kbeg + k) * ld;
       estride = (int64_t)dk * ld;
       step = (int64_t)BK * ld;
     } else {
       k = t % BK;
       i = t / BK;
-      di = 256 / BK;
+      di = NT / BK;
       dk = 0;
       p = base + (kbeg + k) + (x0 + i) * ld;
       estride = (int64_t)di * ld;
@@ -216,28 +217,51 @@ __host__ __device__ __forceinline__ void plain_slab_range(int64_t x0, int64_t X,
   *hi = (int)h;
 }
 
+// Workgroup shapes: eight waves of 64 x 32 for 128 x 128 tiles, four of 32 x 32
+// for 64 x 64.  Both leave four waves on a SIMD (at most 128 registers): with
+// two, waves of one workgroup stop together at every slab's barrier and the
+// MFMA pipe runs at about 60 % (measured with persistent workgroups that hid
+// every load).
+template <int BM>
+struct TileShape {
+  static constexpr int NT = BM == 128 ? 512 : 256;  // threads
+  static constexpr int WC = NT / 128;               // waves across the columns (2 down the rows)
+};
+
 template <int BM, int BN, bool TA, bool TB, int CMP>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
+__global__ __launch_bounds__(TileShape<BM>::NT, 4) void k_gemm(GemmArgs g) {
+  constexpr int NT = TileShape<BM>::NT, WC = TileShape<BM>::WC;
   typedef MfmaTraits<CMP> Tr;
   typedef typename Tr::T T;
   typedef typename Tr::Acc Acc;
   constexpr int BK = 16;
   constexpr int PAD = 1;
-  constexpr int WM = BM / 2, WN = BN / 2, SA = WM / 16, SB = WN / 16;
+  constexpr int WM = BM / 2, WN = BN / WC, SA = WM / 16, SB = WN / 16;
   // op(A) runs along i in memory when A is not transposed; op(B)^T (N x K)
   // runs along j when B is transposed.
   constexpr bool A_ALONG = !TA, B_ALONG = TB;
-  typedef SliceLoader<BM, BK, A_ALONG> LA_t;
-  typedef SliceLoader<BN, BK, B_ALONG> LB_t;
+  typedef SliceLoader<BM, BK, A_ALONG, NT> LA_t;
+  typedef SliceLoader<BN, BK, B_ALONG, NT> LB_t;
   __shared__ T As[2][BK][BM + PAD];
   __shared__ T Bs[2][BK][BN + PAD];
   const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = l >> 4;
   const int wm = w & 1, wn = w >> 1;
   const TileId tid;
   const int64_t i0 = tid.x * BM, j0 = tid.y * BN;
-  const int64_t kbeg = tid.z * g.kchunk;
-  const int64_t kend = min(g.K, kbeg + g.kchunk);
-  const int nslab = (int)((kend - kbeg + BK - 1) / BK);
+  int64_t kbeg = tid.z * g.kchunk;
+  int64_t kend = min(g.K, kbeg + g.kchunk);
+  // Slabs that a structure mask zeroes for the whole tile are left out:
+  // op(A)[x, k] is nonzero only for k <= x (from the tile's last row) or only
+  // for k >= x (from its first), likewise op(B).
+  if (g.maskA != MASK_NONE) {
+    if ((g.maskA == MASK_UNIT_LOWER) == A_ALONG) kend = min(kend, i0 + BM);
+    else kbeg = max(kbeg, i0 / BK * BK);
+  }
+  if (g.maskB != MASK_NONE) {
+    if ((g.maskB == MASK_UNIT_LOWER) == B_ALONG) kend = min(kend, j0 + BN);
+    else kbeg = max(kbeg, j0 / BK * BK);
+  }
+  const int nslab = kend > kbeg ? (int)((kend - kbeg + BK - 1) / BK) : 0;
 
   Acc acc[SA][SB];
 #pragma unroll
@@ -561,13 +585,13 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const double* P, int nspl
 template <int BM, int BN, int CMP>
 static void launch_t(const GemmDesc& d, const GemmArgs& g, dim3 grid, hipStream_t s) {
   if (d.ta == 'N' && d.tb == 'N')
-    hipLaunchKernelGGL((k_gemm<BM, BN, false, false, CMP>), grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, false, false, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
   else if (d.ta == 'T' && d.tb == 'N')
-    hipLaunchKernelGGL((k_gemm<BM, BN, true, false, CMP>), grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, true, false, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
   else if (d.ta == 'N' && d.tb == 'T')
-    hipLaunchKernelGGL((k_gemm<BM, BN, false, true, CMP>), grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, false, true, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
   else
-    hipLaunchKernelGGL((k_gemm<BM, BN, true, true, CMP>), grid, dim3(256), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, true, true, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
 }
 
 template <int BM, int BN>
@@ -582,6 +606,55 @@ static void launch_bf16(const GemmDesc& d, const GemmArgs& g, dim3 grid, hipStre
     hipLaunchKernelGGL((k_gemm_bf16<BM, BN, true, true>), grid, dim3(256), 0, s, g);
 }
 
+// Tile size and split of K.
+static void choose(const GemmDesc& d, int64_t scratch, int64_t* BM, int64_t* nsplit,
+                   int64_t* kchunk) {
+  auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  // 128 x 128 tiles where tiles, or tiles and splits of at least 256, fill the
+  // chip; 64 x 64 otherwise, and for updates of depth 128 and less, which move
+  // more bytes of C than an MFMA time's worth: four small workgroups a CU keep
+  // more of them in flight (12288 x 3072 at depth 128: 234 us against 257 us;
+  // at depth 256 388 against 378 us, at 512 (49152 rows) 2.51 against 2.64 ms).
+  const int64_t t128 = cdiv(d.M, 128) * cdiv(d.N, 128);
+  const bool wide = d.M >= 128 && d.N >= 128;
+  *BM = 64;
+  if (d.compute == COMPUTE_F64) {
+    if (wide && (d.beta == 0.0 ? t128 * std::max<int64_t>(d.K / 256, 1) : (d.K > 128 ? t128 : 0)) >= 256)
+      *BM = 128;
+  } else if (wide && (t128 >= 128 || d.K >= 4096)) {
+    *BM = 128;
+  }
+  const int64_t tiles = cdiv(d.M, *BM) * cdiv(d.N, *BM);
+  // Split of K: the one with the least estimated time, in microseconds.  A slab
+  // takes a workgroup's MFMA time for every workgroup on its CU, and not less
+  // than a memory latency allows; split partials are written, read back and
+  // cost a launch.  (128 x 128 x 16384: 97 us in 32 slices of 512 one tile wide,
+  // 24 us in 64 to 128 slices of four tiles; 128 x 3072 x 12288: 245 us in 576
+  // workgroups, one full and one nearly empty wave of them, 185 us in 504;
+  // 16384 x 64 updates of depth 64: 23 us split in two, 12 us whole.)
+  const double slots = *BM == 64 ? 1024 : 512, mn = (double)d.M * (double)d.N;
+  const int64_t cap = std::min(d.K / (d.K >= 1024 ? 64 : 32), (int64_t)((double)scratch / mn));
+  auto cost = [&](int64_t ns) {
+    const double wgs = (double)(tiles * ns), waves = std::ceil(wgs / slots);
+    const double occ = std::min(slots / 256, std::ceil(wgs / 256));
+    const double slab = *BM == 64 ? std::max(1.6, 0.43 * occ) : (occ > 1 ? 3.4 : 2.6);
+    return waves * (2.0 + (double)d.K / (16.0 * ns) * slab) + (ns > 1 ? 5.0 + ns * mn * 16 / 4e6 : 0);
+  };
+  *nsplit = 1;
+  double best = cost(1);
+  for (int64_t wgs : {64, 128, 256, 512, 1024, 1536, 2048}) {
+    const int64_t ns = std::min(wgs / tiles, cap);
+    if (ns < 2) continue;
+    const double c = cost(ns);
+    if (c < best) {
+      best = c;
+      *nsplit = ns;
+    }
+  }
+  *kchunk = cdiv(cdiv(d.K, *nsplit), 32) * 32;
+  *nsplit = cdiv(d.K, *kchunk);
+}
+
 hipError_t gemm(const GemmDesc& d, hipStream_t s, double* scratch, int64_t scratch_doubles,
                 double* flops) {
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
@@ -590,27 +663,10 @@ hipError_t gemm(const GemmDesc& d, hipStream_t s, double* scratch, int64_t scrat
     // a K = 0 product only happens for empty panels, which callers avoid.
     return hipSuccess;
   }
-  // 128 x 128 tiles when there are enough of them to fill the chip, or when
-  // a long K (split below) supplies the parallelism and the larger tile
-  // halves the operand re-reads; 64 x 64 tiles otherwise.
-  const int64_t t128 = ((d.M + 127) / 128) * ((d.N + 127) / 128);
-  const bool big = d.M >= 128 && d.N >= 128 && (t128 >= 128 || d.K >= 4096);
-  const int BM = big ? 128 : 64, BN = big ? 128 : 64;
-  const int64_t tm = (d.M + BM - 1) / BM, tn = (d.N + BN - 1) / BN;
-  const int64_t tiles = tm * tn;
-  // Split-K when the output has few tiles: slices of at least 512 for long K,
-  // of at least 32 for short K (the small products of a recursion node, whose
-  // one or few workgroups would otherwise walk K alone).
-  int64_t nsplit = 1;
-  const int64_t min_chunk = d.K >= 1024 ? 512 : 32;
-  if (tiles < 512 && d.K >= 2 * min_chunk && scratch && scratch_doubles >= 2 * d.M * d.N) {
-    nsplit = std::min<int64_t>((1024 + tiles - 1) / tiles, d.K / min_chunk);
-    nsplit = std::min<int64_t>(nsplit, scratch_doubles / (d.M * d.N));
-    nsplit = std::max<int64_t>(nsplit, 1);
-  }
-  int64_t kchunk = (d.K + nsplit - 1) / nsplit;
-  kchunk = (kchunk + 31) / 32 * 32;
-  nsplit = (d.K + kchunk - 1) / kchunk;
+  int64_t BM, nsplit, kchunk;
+  choose(d, scratch ? scratch_doubles : 0, &BM, &nsplit, &kchunk);
+  const bool big = BM == 128;
+  const int64_t tm = (d.M + BM - 1) / BM, tn = (d.N + BM - 1) / BM;
   GemmArgs g{d.M, d.N, d.K, kchunk, d.alpha, d.beta, d.A, d.lda, d.B, d.ldb,
              d.C, d.ldc, nsplit > 1 ? scratch : nullptr, d.maskA, d.maskB, d.add_identity};
   dim3 grid((unsigned)tm, (unsigned)tn, (unsigned)nsplit);

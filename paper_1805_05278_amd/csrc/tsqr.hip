@@ -593,15 +593,19 @@ struct HRArgs {
 // operand in registers or one LDS read away: wave c holds column tile c of
 // whatever is being formed, in MFMA accumulator layout, where an accumulator
 // is the B operand of the next product as it stands.
-//   1. X, the top rows of W, column tile by column tile: B <- B - T B along
-//      the path to leaf block 0 (B and every T upper triangular: only tiles on
-//      or above the diagonal), then X = [B; 0] - V (Z B).  No barrier.
+//   1. X, the top rows of W: B <- B - T B along the path to leaf block 0 (B and
+//      every T upper triangular: 20 tile products, shared evenly), then X =
+//      [B; 0] - V (Z B), column tile by column tile.
 //   2. Sign-modified LU of X, right-looking by 16 columns.  The wave that owns
 //      the column tile eliminates its diagonal tile and the tiles below it
 //      together, column by column in registers (the pivot's multipliers are
 //      broadcast inside the FMAs), and L_bb^-1 alongside; the others then take
 //      U_bj = L_bb^-1 X_bj and X_ij -= L_ib U_bj.  One barrier per 16 columns.
-//   3. U^-1 and L^-1 by tiles, T = U S L^-T, R = -S R_root.
+//   3. T = U S L^-T and U^-1 by tiles, by substitution; R = -S R_root.
+// At most 256 registers, accumulation registers included: what one workgroup of
+// the look-ahead's GEMM leaves when it ends.  With 340 the kernel waited for the
+// end of whole update launches (up to 2.8 ms; 355 us on average beside the
+// depth-512 updates of 65536 x 8192).
 //   Measured (MI355X, 64 columns; before: one barrier per pivot, 127 in all,
 // with the rows in registers of four threads each): 84 -> 27 us under 1024 rows,
 // 126 -> 50 us under 1048576 (eleven path steps).  About half of it is the 64
@@ -609,39 +613,12 @@ struct HRArgs {
 struct HrLds {
   double l[10][kTile];    // L, tile (i, b) at tri(b, i); strict lower and, below it, full tiles
   double u[10][kTile];    // U, tile (b, j) at tri(b, j)
-  double li[10][kTile];   // L^-1, tile (i, b) at tri(b, i)
-  double ui[10][kTile];   // U^-1, tile (b, j) at tri(b, j)
+  double li[4][kTile];    // L_bb^-1
+  double ui[4][kTile];    // U_bb^-1
   double sv[kNB];         // S
   double dv[kNB];         // D
 };
 
-// Operand tiles (p, q), p <= q <= c, of a 64 x 64 upper triangle in a slot, as
-// MFMA A operands: lane (g, cl) holds M[16 p + cl][16 q + g + 4 r].
-__device__ __forceinline__ void hr_load_upper(const double* G, int c, int g, int cl,
-                                              double (&m)[10][4]) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (q <= c) {
-#pragma unroll
-      for (int p = 0; p <= q; ++p)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[q * (q + 1) / 2 + p][r] = G[16 * p + cl + (16 * q + g + 4 * r) * kNB];
-    }
-}
-// Column tile c of an upper triangular product: D_p = sum_{p <= q <= c} M_pq B_q.
-__device__ __forceinline__ void hr_mul_upper(const double (&m)[10][4], const d4 (&B)[4], int c,
-                                             d4 (&D)[4]) {
-#pragma unroll
-  for (int p = 0; p < 4; ++p) D[p] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (q <= c) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int p = 0; p <= q; ++p) D[p] = mfma64(m[q * (q + 1) / 2 + p][r], B[q][r], D[p]);
-    }
-}
 // D += A B for an A tile in LDS (row-major) and a B tile in registers.
 __device__ __forceinline__ d4 hr_mul_tile(const double* A, const d4 B, int g, int cl, d4 D) {
 #pragma unroll
@@ -651,6 +628,74 @@ __device__ __forceinline__ d4 hr_mul_tile(const double* A, const d4 B, int g, in
 __device__ __forceinline__ void hr_put_tile(double* S, const d4 v, int g, int cl) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) S[(g + 4 * r) * kTLD + cl] = v[r];
+}
+
+// A product of two 64 x 64 upper triangles takes 20 products of 16 x 16 tiles;
+// wave w forms the output tiles whose five are its share: (p, c) needs tiles
+// (p, q) and (q, c) for q = p .. c.
+struct TriShare {
+  int p[5], q[5], c[5];
+  bool last[5];  // the output tile is complete after this product
+  __device__ explicit TriShare(int w) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      int pp, qq, cc;
+      if (w == 0) { pp = 0; qq = i < 4 ? i : 0; cc = i < 4 ? 3 : 0; }
+      else if (w == 1) { pp = 0; qq = i < 3 ? i : i - 3; cc = i < 3 ? 2 : 1; }
+      else if (w == 2) { pp = 1; qq = i < 3 ? 1 + i : i - 2; cc = i < 3 ? 3 : 2; }
+      else { pp = i < 2 ? 2 : i - 1; qq = i < 2 ? 2 + i : i - 1; cc = i < 2 ? 3 : i - 1; }
+      p[i] = pp;
+      q[i] = qq;
+      c[i] = cc;
+      last[i] = qq == cc;
+    }
+  }
+};
+
+// Its five A operands from an upper triangle in a slot.
+__device__ __forceinline__ void tri_load(const TriShare& sh, const double* T, int g, int cl,
+                                         double (&m)[5][4]) {
+#pragma unroll
+  for (int i = 0; i < 5; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      m[i][r] = (T + 16 * sh.p[i] + 16 * sh.q[i] * kNB)[cl + (g + 4 * r) * kNB];
+}
+// O = A B, -A B or B - A B for the wave's output tiles: A in m, B's and O's
+// tiles in LDS.
+enum TriOut { TRI_POS, TRI_NEG, TRI_SUB };
+template <TriOut OUT>
+__device__ __forceinline__ void tri_mul(const TriShare& sh, const double (&m)[5][4],
+                                        const double (*Bs)[kTile], double (*O)[kTile], int g,
+                                        int cl) {
+  d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const double* bs = Bs[tri(sh.q[i], sh.c[i])];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc = mfma64(m[i][r], bs[(g + 4 * r) * kTLD + cl], acc);
+    if (sh.last[i]) {
+      if constexpr (OUT == TRI_SUB) {
+        const double* bt = Bs[tri(sh.p[i], sh.c[i])];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = bt[(g + 4 * r) * kTLD + cl] - acc[r];
+      }
+      hr_put_tile(O[tri(sh.p[i], sh.c[i])], OUT == TRI_NEG ? -acc : acc, g, cl);
+      acc = d4{0.0, 0.0, 0.0, 0.0};
+    }
+  }
+}
+// B += M, the wave's tiles.
+__device__ __forceinline__ void tri_add(const TriShare& sh, double (*B)[kTile],
+                                        const double (*M)[kTile], int g, int cl) {
+#pragma unroll
+  for (int i = 0; i < 5; ++i)
+    if (sh.last[i]) {
+      double* bt = B[tri(sh.p[i], sh.c[i])];
+      const double* mt = M[tri(sh.p[i], sh.c[i])];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bt[(g + 4 * r) * kTLD + cl] += mt[(g + 4 * r) * kTLD + cl];
+    }
 }
 
 // Step J of the elimination of a 16-column tile whose diagonal tile sits in
@@ -696,7 +741,7 @@ __device__ __forceinline__ void hr_uinv(const double (&u)[16], const double (&zs
   }
 }
 
-__global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
+__global__ __launch_bounds__(256, 2) void k_tsqr_hr(HRArgs a) {
   __shared__ HrLds S;
   const int t = threadIdx.x, c = __builtin_amdgcn_readfirstlane(t >> 6);
   const int l = t & 63, g = l >> 4, cl = l & 15;
@@ -717,26 +762,18 @@ __global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
   };
   d4 x[4];
   {
-    d4 B[4], D[4];
-    double ta[10][4], tb[10][4];
+    // B in turn in the tiles that L and U take later.
+    const TriShare sh(c);
+    double ta[5][4];
+    tri_load(sh, path(0), g, cl, ta);
 #pragma unroll
     for (int p = 0; p < 4; ++p)
+      if (p <= c) {  // B = I, column tile c
+        d4 v = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int r = 0; r < 4; ++r) B[p][r] = (p == c && g + 4 * r == cl && 16 * c + cl < nbr) ? 1.0 : 0.0;
-    hr_load_upper(path(0), c, g, cl, ta);
-    // Step k's T is loaded while step k - 1 is multiplied.
-    for (int k = 0; k + 1 < np; k += 2) {
-      hr_load_upper(path(k + 1), c, g, cl, tb);
-      hr_mul_upper(ta, B, c, D);
-#pragma unroll
-      for (int p = 0; p < 4; ++p) B[p] -= D[p];
-      if (k + 2 < np) {
-        hr_load_upper(path(k + 2), c, g, cl, ta);
-        hr_mul_upper(tb, B, c, D);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) B[p] -= D[p];
+        for (int r = 0; r < 4; ++r) v[r] = (p == c && g + 4 * r == cl && 16 * c + cl < nbr) ? 1.0 : 0.0;
+        hr_put_tile(S.l[tri(p, c)], v, g, cl);
       }
-    }
     // V_top of leaf block 0 (unit lower), tiles (p, q), q <= min(p, c).
     double v[10][4];
 #pragma unroll
@@ -752,19 +789,38 @@ __global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
                 (row < nbr && col < nbr) ? (row > col ? av : (row == col ? 1.0 : 0.0)) : 0.0;
           }
         }
-    if (np & 1) hr_mul_upper(ta, B, c, D);  // M = Z B
-    else hr_mul_upper(tb, B, c, D);
+    double (*Bt)[kTile] = S.l, (*Mt)[kTile] = S.u;  // B, and the other buffer
+    lds_barrier();
+    for (int k = 0; k + 1 < np; ++k) {
+      tri_mul<TRI_SUB>(sh, ta, Bt, Mt, g, cl);  // B - T B
+      tri_load(sh, path(k + 1), g, cl, ta);
+      lds_barrier();
+      double (*const x)[kTile] = Bt;
+      Bt = Mt;
+      Mt = x;
+    }
+    tri_mul<TRI_NEG>(sh, ta, Bt, Mt, g, cl);  // -Z B
+    lds_barrier();
+    // Column tile c of X = [B; 0] - V (Z B).
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+      x[p] = d4{0.0, 0.0, 0.0, 0.0};
+      if (p <= c) {
 #pragma unroll
-      for (int q = 0; q <= p; ++q)
-        if (q <= c) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc = mfma64(v[p * (p + 1) / 2 + q][r], D[q][r], acc);
-        }
-      x[p] = B[p] - acc;
+        for (int r = 0; r < 4; ++r) x[p][r] = Bt[tri(p, c)][(g + 4 * r) * kTLD + cl];
+      }
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q <= c) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double m = Mt[tri(q, c)][(g + 4 * r) * kTLD + cl];
+#pragma unroll
+          for (int p = q; p < 4; ++p) x[p] = mfma64(v[p * (p + 1) / 2 + q][r], m, x[p]);
+        }
+      }
+    lds_barrier();
   }
   // Sign-modified LU.  Slot k of x is row tile b + k (rotated every step).
   for (int b = 0; b < nsub; ++b) {
@@ -792,7 +848,7 @@ __global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
       if (g == 0) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          S.li[tri(b, b)][i * kTLD + cl] = e[i];
+          S.li[b][i * kTLD + cl] = e[i];
           lt[i * kTLD + cl] = xc[i] * z;  // L below the diagonal
         }
         S.sv[16 * b + cl] = sgn;
@@ -818,11 +874,11 @@ __global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           S.u[tri(b, b)][i * kTLD + cl] = xc[i];
-          S.ui[tri(b, b)][i * kTLD + cl] = m[i];
+          S.ui[b][i * kTLD + cl] = m[i];
         }
       }
     } else if (c > b && c < nsub) {
-      const d4 u = hr_mul_tile(S.li[tri(b, b)], x[0], g, cl, d4{0.0, 0.0, 0.0, 0.0});
+      const d4 u = hr_mul_tile(S.li[b], x[0], g, cl, d4{0.0, 0.0, 0.0, 0.0});
       hr_put_tile(S.u[tri(b, c)], u, g, cl);
 #pragma unroll
       for (int k = 1; k < 4; ++k)
@@ -840,89 +896,76 @@ __global__ __launch_bounds__(256) void k_tsqr_hr(HRArgs a) {
     if (a.sign) a.sign[t] = d;
   }
   lds_barrier();
-  // Column tile c of L^-1 and U^-1:
-  //   (L^-1)_ic = -L_ii^-1 sum_{c <= q < i} L_iq (L^-1)_qc,  i = c + 1 ..
-  //   (U^-1)_ic = -U_ii^-1 sum_{i < q <= c} U_iq (U^-1)_qc,  i = c - 1 .. 0
-  if (c < nsub) {
-    d4 y[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) y[0][r] = S.li[tri(c, c)][(g + 4 * r) * kTLD + cl];
-#pragma unroll
-    for (int k = 1; k < 4; ++k) {
-      const int i = c + k;
-      if (i < nsub) {
-        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < k; ++q) acc = hr_mul_tile(S.l[tri(c + q, i)], y[q], g, cl, acc);
-        y[k] = hr_mul_tile(S.li[tri(i, i)], -acc, g, cl, d4{0.0, 0.0, 0.0, 0.0});
-        hr_put_tile(S.li[tri(c, i)], y[k], g, cl);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) y[0][r] = S.ui[tri(c, c)][(g + 4 * r) * kTLD + cl];
-#pragma unroll
-    for (int k = 1; k < 4; ++k) {
-      const int i = c - k;
-      if (i >= 0) {
-        d4 acc = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < k; ++q) acc = hr_mul_tile(S.u[tri(i, c - q)], y[q], g, cl, acc);
-        y[k] = hr_mul_tile(S.ui[tri(i, i)], -acc, g, cl, d4{0.0, 0.0, 0.0, 0.0});
-        hr_put_tile(S.ui[tri(i, c)], y[k], g, cl);
-      }
-    }
-  }
-  lds_barrier();
   double rtop[kTS / 256];  // the root's R, for the last step
 #pragma unroll
   for (int i = 0; i < kTS / 256; ++i) rtop[i] = a.Rtop[t + 256 * i];
-  // T_pc = sum_{p <= k <= c} U_pk S_k (L^-1)_ck^T.
   if (c < nsub) {
-    d4 acc[4];
+    // Row tile c of T = U S L^-T, as column tile c of T^T, by substitution:
+    //   (T^T)_kc = L_kk^-1 (S_k U_ck^T - sum_{c <= q < k} L_kq (T^T)_qc),  k = c ..
+    // and column tile c of U^-1, into the downsweep's input:
+    //   (U^-1)_ic = -U_ii^-1 sum_{i < q <= c} U_iq (U^-1)_qc,  i = c - 1 .. 0
+    d4 y[4];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) acc[p] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < 4; ++k) {
+      const int i = c + k;
+      if (i < nsub) {
+        d4 acc;
+        const double* ut = S.u[tri(c, i)];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (k <= c) {
-        const double* lt = S.li[tri(k, c)];
+        for (int r = 0; r < 4; ++r) acc[r] = -S.sv[16 * i + g + 4 * r] * ut[cl * kTLD + g + 4 * r];
+#pragma unroll
+        for (int q = 0; q < k; ++q) acc = hr_mul_tile(S.l[tri(c + q, i)], y[q], g, cl, acc);
+        y[k] = hr_mul_tile(S.li[i], -acc, g, cl, d4{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int e = cl * kTLD + g + 4 * r;
-          const double bv = S.sv[16 * k + g + 4 * r] * lt[e];
-#pragma unroll
-          for (int p = 0; p <= k; ++p) acc[p] = mfma64(S.u[tri(p, k)][e], bv, acc[p]);
+          const int row = 16 * c + cl, cc = 16 * i + g + 4 * r;
+          if (row < nbr && cc < nbr) a.Tp[row + cc * a.ldt] = (row <= cc) ? y[k][r] : 0.0;
         }
       }
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
+    }
+    for (int i = 0; i < c; ++i)  // tiles below T's diagonal
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = 16 * p + g + 4 * r, cc = 16 * c + cl;
-        if (row < nbr && cc < nbr) a.Tp[row + cc * a.ldt] = (row <= cc) ? acc[p][r] : 0.0;
+        const int row = 16 * c + cl, cc = 16 * i + g + 4 * r;
+        if (row < nbr && cc < nbr) a.Tp[row + cc * a.ldt] = 0.0;
       }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[0][r] = S.ui[c][(g + 4 * r) * kTLD + cl];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = c - k;
+      if (i >= 0) {
+        if (k > 0) {
+          d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int q = 0; q < k; ++q) acc = hr_mul_tile(S.u[tri(i, c - q)], y[q], g, cl, acc);
+          y[k] = hr_mul_tile(S.ui[i], -acc, g, cl, d4{0.0, 0.0, 0.0, 0.0});
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * i + g + 4 * r, cc = 16 * c + cl;
+          if (cc < nbr) a.Broot[row + cc * kNB] = (row <= cc) ? y[k][r] : 0.0;
+        }
+      }
+    }
   }
-  // The final L (strict lower) and R of the top rows, and the downsweep's
-  // input [U^-1 | -S D].  Branch-free, so that the LDS reads overlap.
+  // The final L (strict lower) and R of the top rows.  Branch-free, so that the
+  // LDS reads overlap.
   const double ds = -S.dv[t & 63] * S.sv[t & 63];
 #pragma unroll
   for (int i = 0; i < kTS / 256; ++i) {
     const int r = t & 63, cc = (t >> 6) + 4 * i;
     const int tl = (r & 15) * kTLD + (cc & 15), rt = r >> 4, ct = cc >> 4;
-    const bool up = r <= cc, in = r < nbr && cc < nbr;
     const double lv = S.l[tri(min(rt, ct), max(rt, ct))][tl];
-    const double uv = S.ui[tri(min(rt, ct), max(rt, ct))][tl];
-    a.LR[t + 256 * i] = in ? (up ? ds * rtop[i] : lv) : 0.0;
-    a.Broot[t + 256 * i] = (in && up) ? uv : 0.0;
+    a.LR[t + 256 * i] = (r < nbr && cc < nbr) ? (r <= cc ? ds * rtop[i] : lv) : 0.0;
   }
-  if (a.nq > nbr) {
-    // Columns nbr .. 2 nbr - 1 (from column nbr of the slot, which may lie
-    // inside the first kNB columns).
-    __syncthreads();
+  // With Q the downsweep also starts from -S D, columns nbr .. 2 nbr - 1 of
+  // its input (it reads nothing below the diagonal, and no U^-1 beyond nbr).
+  if (a.nq > nbr)
     for (int e = t; e < kNB * nbr; e += 256) {
       const int r = e % kNB, cc = e / kNB;
       a.Broot[r + (nbr + cc) * kNB] = (r == cc && r < nbr) ? ds : 0.0;
     }
-  }
 }
 
 struct DownArgs {
@@ -938,28 +981,6 @@ struct DownArgs {
   double* Q;             // optional
   int64_t ldq;
   int nbr;
-};
-
-// A product of two 64 x 64 upper triangles takes 20 products of 16 x 16 tiles;
-// wave w forms the output tiles whose five are its share: (p, c) needs tiles
-// (p, q) and (q, c) for q = p .. c.
-struct TriShare {
-  int p[5], q[5], c[5];
-  bool last[5];  // the output tile is complete after this product
-  __device__ explicit TriShare(int w) {
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      int pp, qq, cc;
-      if (w == 0) { pp = 0; qq = i < 4 ? i : 0; cc = i < 4 ? 3 : 0; }
-      else if (w == 1) { pp = 0; qq = i < 3 ? i : i - 3; cc = i < 3 ? 2 : 1; }
-      else if (w == 2) { pp = 1; qq = i < 3 ? 1 + i : i - 2; cc = i < 3 ? 3 : 2; }
-      else { pp = i < 2 ? 2 : i - 1; qq = i < 2 ? 2 + i : i - 1; cc = i < 2 ? 3 : i - 1; }
-      p[i] = pp;
-      q[i] = qq;
-      c[i] = cc;
-      last[i] = qq == cc;
-    }
-  }
 };
 
 // Row `row` (per lane) of the basis as operands of a contraction over its
@@ -1017,13 +1038,6 @@ __global__ __launch_bounds__(256, 2) void k_tsqr_down(DownArgs a) {
   const int b1 = min(b0 + a.chain_len[0], a.nblocks[0]);
   const TriShare sh(w);
   double ta[5][4], ya[5][4];
-  auto load_t = [&](const double* T) {
-#pragma unroll
-    for (int i = 0; i < 5; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        ta[i][r] = (T + 16 * sh.p[i] + 16 * sh.q[i] * kNB)[cl + (g + 4 * r) * kNB];
-  };
   // A child's basis (leading dim kYL).  Narrow panels read past the child's
   // rows and columns (inside the workspace: the level's R follows its Y) and
   // mask what they read.
@@ -1034,30 +1048,6 @@ __global__ __launch_bounds__(256, 2) void k_tsqr_down(DownArgs a) {
       for (int r = 0; r < 4; ++r) {
         const double v = (Y + 16 * sh.p[i] + 16 * sh.q[i] * kYL)[cl + (g + 4 * r) * kYL];
         ya[i][r] = (16 * sh.p[i] + cl < nbr && 16 * sh.q[i] + g + 4 * r < nbr) ? v : 0.0;
-      }
-  };
-  // O = sgn A B for this wave's output tiles: A in m, B's tiles in LDS.
-  auto mul = [&](const double (&m)[5][4], double (*Bs)[kTile], double (*O)[kTile], bool neg) {
-    d4 acc = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const double* bs = Bs[tri(sh.q[i], sh.c[i])];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc = mfma64(m[i][r], bs[(g + 4 * r) * kTLD + cl], acc);
-      if (sh.last[i]) {
-        hr_put_tile(O[tri(sh.p[i], sh.c[i])], neg ? -acc : acc, g, cl);
-        acc = d4{0.0, 0.0, 0.0, 0.0};
-      }
-    }
-  };
-  auto sub_m = [&]() {  // B <- B - M, this wave's tiles
-#pragma unroll
-    for (int i = 0; i < 5; ++i)
-      if (sh.last[i]) {
-        double* bt = Bt[tri(sh.p[i], sh.c[i])];
-        const double* mt = Mt[tri(sh.p[i], sh.c[i])];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bt[(g + 4 * r) * kTLD + cl] += mt[(g + 4 * r) * kTLD + cl];
       }
   };
   // The path's nodes, lane k's at level k (integer divisions are slow: once,
@@ -1072,7 +1062,7 @@ __global__ __launch_bounds__(256, 2) void k_tsqr_down(DownArgs a) {
   };
   auto load_level_t = [&](int lev) {  // level 0: the last block of the chain
     const int node = lev == 0 ? b1 - 1 : __builtin_amdgcn_readlane(path, lev);
-    load_t(a.T[lev] + (int64_t)node * kTS);
+    tri_load(sh, a.T[lev] + (int64_t)node * kTS, g, cl, ta);
   };
   auto load_level_y = [&](int lev) {
     int pos;
@@ -1103,12 +1093,12 @@ __global__ __launch_bounds__(256, 2) void k_tsqr_down(DownArgs a) {
     int pos;
     const int node = node_at(lev, &pos);
     const bool single = min(a.chain_len[lev], a.nblocks[lev] - node * a.chain_len[lev]) < 2;
-    if (!single) mul(ta, Bt, Mt, true);
+    if (!single) tri_mul<TRI_NEG>(sh, ta, Bt, Mt, g, cl);
     load_level_t(lev - 1);
     lds_barrier();
     if (!single) {
-      if (pos == 0) sub_m();
-      else mul(ya, Mt, Bt, false);
+      if (pos == 0) tri_add(sh, Bt, Mt, g, cl);
+      else tri_mul<TRI_POS>(sh, ya, Mt, Bt, g, cl);
     }
     if (lev > 1) load_level_y(lev - 1);
     lds_barrier();
@@ -1124,10 +1114,10 @@ __global__ __launch_bounds__(256, 2) void k_tsqr_down(DownArgs a) {
     int r0 = 16 * (w + 4 * part);
     double y[4][4];
     down_load_row(Ab, a.lda, min(r0 + cl, rows - 1), nbr, nsub, g, y);
-    mul(ta, Bt, Mt, true);
-    if (!first) load_t(a.T[0] + (int64_t)(b - 1) * kTS);
+    tri_mul<TRI_NEG>(sh, ta, Bt, Mt, g, cl);
+    if (!first) tri_load(sh, a.T[0] + (int64_t)(b - 1) * kTS, g, cl, ta);
     lds_barrier();
-    if (!first) sub_m();
+    if (!first) tri_add(sh, Bt, Mt, g, cl);
     for (; r0 < rows; r0 += rstep) {
       const int row = min(r0 + cl, rows - 1);
       const bool in = r0 + cl < rows, top = first && r0 < 64;

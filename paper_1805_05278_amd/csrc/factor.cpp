@@ -36,6 +36,8 @@ FactorWs carve_factor(double* base, const FactorLayout& L) {
   w.ua1 = take(L.ua1);
   w.ua2 = take(L.ua2);
   w.scratch_aux = take(L.scratch_aux);
+  w.tw = take(L.tw);
+  w.tw_n = L.tw;
   w.w_cap = L.wa;
   w.scratch_n = L.scratch;
   w.u_cap = L.u1;
@@ -211,15 +213,32 @@ hipError_t factor_blocked(hipStream_t s, const Lookahead& la, const Tuning& t, c
   double* A = a.A;
   const int64_t lda = a.lda;
   const bool single = n <= t.bstar && m > n;
-  auto factor_panel = [&](int64_t j) -> hipError_t {
-    const int64_t wd = std::min(nb, n - j);
+  // The steps: panels of nb, or several of them together (step_width).  A wide
+  // step's T goes to the workspace, two steps in turn: the next step is
+  // factored while the look-ahead stream still reads this one's.
+  struct Step {
+    int64_t j, wd;
+    double* T;
+    int64_t ldt;
+  };
+  int odd = 0;
+  auto step_at = [&](int64_t j) {
+    Step p{j, step_width(m, n, j, t), a.T + j * a.ldt, a.ldt};
+    if (p.wd > nb) {
+      p.T = w.tw + odd * (w.tw_n / 2);
+      p.ldt = p.wd;
+      odd ^= 1;
+    }
+    return p;
+  };
+  auto factor_panel = [&](const Step& p) -> hipError_t {
     EgCtx e;
     e.s = s;
     e.A = A;
     e.lda = lda;
-    e.T = a.T + j * a.ldt;
-    e.t0 = j;
-    e.ldt = a.ldt;
+    e.T = p.T;
+    e.t0 = p.j;
+    e.ldt = p.ldt;
     e.tune = &t;
     e.w = &w;
     e.update_compute = a.update_compute;
@@ -231,29 +250,32 @@ hipError_t factor_blocked(hipStream_t s, const Lookahead& la, const Tuning& t, c
       e.normalize = a.normalize;
       e.sign = a.sign;
     }
-    eg(e, j, j, m - j, wd, false);
+    if (p.wd > nb && p.wd * p.wd > w.tw_n / 2) return hipErrorInvalidValue;
+    eg(e, p.j, p.j, m - p.j, p.wd, false);
+    if (p.wd > nb && e.err == hipSuccess)
+      copy_diagonal_blocks(s, p.wd, nb, p.T, p.ldt, a.T + p.j * a.ldt, a.ldt);
     return e.err;
   };
-  // Trailing update of panel j on columns [c1, c2).
-  auto update = [&](hipStream_t st, int64_t j, int64_t c1, int64_t c2, double* W1, double* W2,
+  // Trailing update of step p on columns [c1, c2).
+  auto update = [&](hipStream_t st, const Step& p, int64_t c1, int64_t c2, double* W1, double* W2,
                     int64_t cap, double* sc, int64_t scn) -> hipError_t {
-    const int64_t wd = std::min(nb, n - j), nc = c2 - c1;
+    const int64_t nc = c2 - c1;
     if (nc <= 0) return hipSuccess;
-    if (wd * nc > cap) return hipErrorInvalidValue;
-    return wy_update(st, m - j, wd, nc, A + j + j * lda, lda, a.T + j * a.ldt, a.ldt, 'T',
-                     A + j + c1 * lda, lda, W1, W2, sc, scn, a.update_compute, flops);
+    if (p.wd * nc > cap) return hipErrorInvalidValue;
+    return wy_update(st, m - p.j, p.wd, nc, A + p.j + p.j * lda, lda, p.T, p.ldt, 'T',
+                     A + p.j + c1 * lda, lda, W1, W2, sc, scn, a.update_compute, flops);
   };
   constexpr int64_t kAuxChunk = 3072;  // columns per look-ahead update launch group
   const bool ahead = t.lookahead && la.aux && la.ev_panel && la.ev_update;
-  hipError_t e = factor_panel(0);
-  for (int64_t j = 0; j < n && e == hipSuccess; j += nb) {
-    const int64_t wd = std::min(nb, n - j);
-    const int64_t c1 = j + wd;                       // first column of panel k + 1
-    if (c1 >= n) break;
-    const int64_t c2 = std::min(n, c1 + nb);         // end of panel k + 1
+  Step cur = step_at(0);
+  hipError_t e = factor_panel(cur);
+  while (e == hipSuccess && cur.j + cur.wd < n) {
+    const Step next = step_at(cur.j + cur.wd);
+    const int64_t c1 = next.j;            // first column of the next step
+    const int64_t c2 = c1 + next.wd;      // end of it
     if (ahead && c2 < n) {
-      // The columns beyond panel k + 1 go to the second stream once panel k
-      // is factored; panel k + 1 is updated and factored here meanwhile.
+      // The columns beyond the next step go to the second stream once this one
+      // is factored; the next is updated and factored here meanwhile.
       e = hipEventRecord(la.ev_panel, s);
       if (e == hipSuccess) e = hipStreamWaitEvent(la.aux, la.ev_panel, 0);
       // In column chunks: a blocked TSQR workgroup needs a CU with no GEMM
@@ -262,23 +284,24 @@ hipError_t factor_blocked(hipStream_t s, const Lookahead& la, const Tuning& t, c
       // best: 16384^2 alone 245 -> 233 ms; 2048 and 4096 in between, 1024
       // slower than no chunks).
       for (int64_t cc = c2; cc < n && e == hipSuccess; cc += kAuxChunk)
-        e = update(la.aux, j, cc, std::min<int64_t>(n, cc + kAuxChunk), w.ua1, w.ua2, w.ua_cap,
+        e = update(la.aux, cur, cc, std::min<int64_t>(n, cc + kAuxChunk), w.ua1, w.ua2, w.ua_cap,
                    w.scratch_aux, w.scratch_aux_n);
       if (e == hipSuccess) e = hipEventRecord(la.ev_update, la.aux);
-      if (e == hipSuccess) e = update(s, j, c1, c2, w.u1, w.u2, w.u_cap, w.scratch, w.scratch_n);
-      if (e == hipSuccess) e = factor_panel(c1);
+      if (e == hipSuccess) e = update(s, cur, c1, c2, w.u1, w.u2, w.u_cap, w.scratch, w.scratch_n);
+      if (e == hipSuccess) e = factor_panel(next);
       if (e == hipSuccess) e = hipStreamWaitEvent(s, la.ev_update, 0);
     } else {
       if (ahead) {
-        e = update(s, j, c1, n, w.u1, w.u2, w.u_cap, w.scratch, w.scratch_n);
+        e = update(s, cur, c1, n, w.u1, w.u2, w.u_cap, w.scratch, w.scratch_n);
       } else {
         // One stream: the whole trailing matrix at once (its temporaries are
         // the look-ahead stream's, sized for every column after the first
         // panel).
-        e = update(s, j, c1, n, w.ua1, w.ua2, w.ua_cap, w.scratch_aux, w.scratch_aux_n);
+        e = update(s, cur, c1, n, w.ua1, w.ua2, w.ua_cap, w.scratch_aux, w.scratch_aux_n);
       }
-      if (e == hipSuccess) e = factor_panel(c1);
+      if (e == hipSuccess) e = factor_panel(next);
     }
+    cur = next;
   }
   return e;
 }

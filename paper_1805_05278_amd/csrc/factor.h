@@ -21,7 +21,8 @@ struct FactorWs {
   double* ua1 = nullptr;
   double* ua2 = nullptr;
   double* scratch_aux = nullptr;
-  int64_t w_cap = 0, scratch_n = 0, u_cap = 0, ua_cap = 0, scratch_aux_n = 0;
+  double* tw = nullptr;
+  int64_t w_cap = 0, scratch_n = 0, u_cap = 0, ua_cap = 0, scratch_aux_n = 0, tw_n = 0;
   int64_t doubles = 0;  // extent of the carved regions
 };
 FactorWs carve_factor(double* base, const FactorLayout& L);

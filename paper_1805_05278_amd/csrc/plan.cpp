@@ -91,24 +91,44 @@ int64_t top_panel(const Tuning& t, int64_t n) {
 
 }  // namespace
 
+int64_t step_width(int64_t m, int64_t n, int64_t j, const Tuning& t) {
+  const int64_t nb = top_panel(t, n), last = std::min(nb, n - j);
+  if (t.t_layout != T_BLOCKED || !t.lookahead) return last;
+  // An update of depth nb reads and writes the trailing matrix once per nb
+  // columns; at depth 128 that takes as long as its MFMA work.  Twice the
+  // depth pays while the updates, not the panels, take the time: from about
+  // 6e7 trailing entries (MI355X: 16384^2 at nb = 128 177 ms, 161 with steps of
+  // 256 down to 6e7 entries, 165 to 1.5e8, 163 with steps of 512; 12288^2 94.7
+  // and 90.7 ms; 65536 x 8192 at nb = 128 215 and 185 ms; 8192^2 45.7 and 45.7).
+  constexpr int64_t kWide = 256;
+  constexpr double kEntries = 6e7;
+  const int64_t w = kWide / nb * nb;
+  if (w <= nb || n - j < 2 * w || (double)(m - j) * (double)(n - j) < kEntries) return last;
+  return w;
+}
+
 FactorLayout factor_layout(int64_t m, int64_t n, const Tuning& t, bool with_q) {
   FactorLayout L;
   const int64_t nb = top_panel(t, n);
   // Every top-level panel is a width-nb problem (the last may be narrower).
-  for (int64_t j = 0; j < n; j += nb) {
-    const int64_t w = std::min(nb, n - j);
+  int64_t wide = nb;  // widest step
+  for (int64_t j = 0; j < n;) {
+    const int64_t w = step_width(m, n, j, t);
     max_panel_ws(m - j, w, t, &L.tsqr);
     L.wa = std::max(L.wa, max_node_product(w, t));
+    wide = std::max(wide, w);
+    j += w;
   }
   L.wa = std::max<int64_t>(L.wa, 1);
   L.wb = L.wa;
   // Split-K partials: room for 512 splits of a 128 x 128 product.
   L.scratch = std::max<int64_t>(int64_t(8) << 20, 4 * L.wa);
   if (t.t_layout == T_BLOCKED && nb < n) {
-    L.u1 = nb * nb;
-    L.u2 = nb * nb;
-    L.scratch = std::max<int64_t>(L.scratch, 4 * nb * nb);
-    const int64_t rest = nb * std::max<int64_t>(n - nb, 1);
+    L.u1 = wide * wide;
+    L.u2 = wide * wide;
+    L.scratch = std::max<int64_t>(L.scratch, 4 * wide * wide);
+    const int64_t rest = wide * std::max<int64_t>(n - nb, 1);
+    if (wide > nb) L.tw = 2 * wide * wide;
     L.ua1 = rest;
     L.ua2 = rest;
     L.scratch_aux = std::max<int64_t>(int64_t(8) << 20, 2 * rest);
@@ -122,7 +142,7 @@ FactorLayout factor_layout(int64_t m, int64_t n, const Tuning& t, bool with_q) {
   }
   auto al = [](int64_t v) { return (v + 31) & ~int64_t(31); };
   L.total = al(L.tsqr) + al(L.wa) + al(L.wb) + al(L.scratch) + al(L.u1) + al(L.u2) + al(L.ua1) +
-            al(L.ua2) + al(L.scratch_aux) + 128;
+            al(L.ua2) + al(L.scratch_aux) + al(L.tw) + 128;
   return L;
 }
 
@@ -439,12 +459,13 @@ std::string describe_plan(int64_t m, int64_t n, const Tuning& t) {
                 "\"cost\":{\"seconds\":%.9g,\"panels\":%lld,\"gemm_flops\":%.9g,"
                 "\"critical_s\":%.9g,\"update_s\":%.9g},"
                 "\"layout\":{\"tsqr\":%lld,\"wa\":%lld,\"wb\":%lld,\"scratch\":%lld,\"u1\":%lld,"
-                "\"u2\":%lld,\"ua1\":%lld,\"ua2\":%lld,\"scratch_aux\":%lld,\"total\":%lld},",
+                "\"u2\":%lld,\"ua1\":%lld,\"ua2\":%lld,\"scratch_aux\":%lld,\"tw\":%lld,\"total\":%lld},",
                 (long long)m, (long long)n, (long long)t.b, t.bstar, (long long)t.nb, t.leaf_rows,
                 t.chain, t.arity, t.t_layout, t.lookahead, e.seconds, (long long)e.panels,
                 e.gemm_flops, e.critical_s, e.update_s, (long long)L.tsqr,
                 (long long)L.wa, (long long)L.wb, (long long)L.scratch, (long long)L.u1,
                 (long long)L.u2, (long long)L.ua1, (long long)L.ua2, (long long)L.scratch_aux,
+                (long long)L.tw,
                 (long long)L.total);
   s += buf;
   // The cost model's features (one-stream counts) and coefficients.
@@ -477,7 +498,8 @@ std::string describe_plan(int64_t m, int64_t n, const Tuning& t) {
   std::snprintf(buf, sizeof buf, ",\"overlap\":%.9g},", cost_coeffs().overlap);
   s += buf;
   // Recursion nodes [c0, rows, width, n1] (n1 = 0: base-case TSQR panel) of
-  // every top-level panel.
+  // every top-level panel (a wide step of the look-ahead joins several of
+  // them, with the same TSQR panels).
   s += "\"nodes\":[";
   bool first = true;
   const int64_t nb = top_panel(t, n);

@@ -51,6 +51,12 @@ TsqrGeom tsqr_geometry(int64_t rows, int w, int leaf_rows, int chain, int arity)
 // b*.  Any split gives the same factors in exact arithmetic.
 int64_t eg_split(int64_t nk, const Tuning& t);
 
+// Width of the right-looking top level's step at column j (BLOCKED): nb, or
+// with look-ahead several panels of nb factored together by Alg. 2 and applied
+// as one update, while the trailing matrix is large.  T keeps its nb x nb
+// diagonal blocks: those of the wider step's T.
+int64_t step_width(int64_t m, int64_t n, int64_t j, const Tuning& t);
+
 // Workspace regions of one factorisation, in doubles, in this order.
 struct FactorLayout {
   int64_t tsqr = 0;     // TSQR plan of the largest panel
@@ -62,6 +68,7 @@ struct FactorLayout {
   int64_t ua1 = 0;      // the same for the look-ahead stream
   int64_t ua2 = 0;
   int64_t scratch_aux = 0;
+  int64_t tw = 0;       // T of two wide steps (BLOCKED with step_width > nb)
   int64_t total = 0;
 };
 // with_q: room for forming the explicit thin Q after the factorisation.

@@ -8,6 +8,10 @@ namespace miqr {
 // Zero the strict lower triangle of each nb x nb diagonal block of a matrix
 // with n columns (nb = n: the strict lower triangle of an n x n matrix).
 void zero_block_lower(hipStream_t s, int64_t n, int64_t nb, double* T, int64_t ldt);
+// The nb x nb diagonal blocks of the w x w upper triangular X into the nb-row
+// layout of a BLOCKED T (w columns at T; zero below the diagonals).
+void copy_diagonal_blocks(hipStream_t s, int64_t w, int64_t nb, const double* X, int64_t ldx,
+                          double* T, int64_t ldt);
 // Q = [I_n; 0] (m x n).
 void set_identity(hipStream_t s, int64_t m, int64_t n, double* Q, int64_t ldq);
 // Copy an m x n matrix.

@@ -37,6 +37,17 @@ __global__ __launch_bounds__(256) void k_zero_block_lower(int64_t n, int64_t nb,
   }
 }
 
+// Upper triangles of the nb x nb diagonal blocks of a w x w matrix into the
+// nb-row layout of the panels' kernels (zero below the diagonals).
+__global__ __launch_bounds__(256) void k_copy_diagonal_blocks(int64_t w, int64_t nb,
+                                                              const double* X, int64_t ldx,
+                                                              double* T, int64_t ldt) {
+  MIQR_FOR_ELEMENTS(nb, w) {
+    const int64_t c = j % nb, b = j - c;
+    if (b + i < w) T[i + j * ldt] = i <= c ? X[b + i + j * ldx] : 0.0;
+  }
+}
+
 __global__ __launch_bounds__(256) void k_set_identity(int64_t m, int64_t n, double* Q,
                                                       int64_t ldq) {
   MIQR_FOR_ELEMENTS(m, n) { Q[i + j * ldq] = (i == j) ? 1.0 : 0.0; }
@@ -172,6 +183,13 @@ void zero_block_lower(hipStream_t s, int64_t n, int64_t nb, double* T, int64_t l
   if (n <= 0 || nb <= 0) return;
   TimedLaunch tl(s, "zero_block_lower", 4.0 * (double)nb * n, 0.0);
   hipLaunchKernelGGL(k_zero_block_lower, Grid2(nb, n).g, dim3(256), 0, s, n, nb, T, ldt);
+}
+
+void copy_diagonal_blocks(hipStream_t s, int64_t w, int64_t nb, const double* X, int64_t ldx,
+                          double* T, int64_t ldt) {
+  if (w <= 0 || nb <= 0) return;
+  TimedLaunch tl(s, "copy_diagonal_blocks", 16.0 * (double)nb * w, 0.0);
+  hipLaunchKernelGGL(k_copy_diagonal_blocks, Grid2(nb, w).g, dim3(256), 0, s, w, nb, X, ldx, T, ldt);
 }
 
 void set_identity(hipStream_t s, int64_t m, int64_t n, double* Q, int64_t ldq) {

@@ -633,6 +633,7 @@ miqr_status miqr_destroy(miqr_handle h) {
   if (h->pin_tasks) hipHostFree(h->pin_tasks);
   if (h->pin_status) hipHostFree(h->pin_status);
   if (h->table_ev) hipEventDestroy(h->table_ev);
+  batch_fork_destroy(&h->fork);
   if (h->ev_panel) hipEventDestroy(h->ev_panel);
   if (h->ev_update) hipEventDestroy(h->ev_update);
   if (h->aux) hipStreamDestroy(h->aux);
@@ -1072,6 +1073,14 @@ miqr_status qr_lstsq_batched_ex(miqr_handle h, void* stream, int64_t count,
     off += ((items[i].n * items[i].n + 31) & ~int64_t(31)) +
            ((items[i].n * items[i].nrhs + 31) & ~int64_t(31));
   }
+  // The queues side by side, except under the per-kernel timer (whose events
+  // sit on the caller's stream) and in a capture of the caller's.
+  const BatchFork* fork = nullptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (!h->profiling && hipStreamIsCapturing(s, &cap) == hipSuccess &&
+      cap == hipStreamCaptureStatusNone && (h->fork.begin || batch_fork_create(&h->fork) == hipSuccess))
+    fork = &h->fork;
+  (void)hipGetLastError();
   // Enqueue the items of `sel` in precision p: tasks grouped by queue (the
   // refinement kernel takes queues 1..3 as one contiguous range), largest
   // problems first within each queue (their cost is about blocks x columns^2
@@ -1124,7 +1133,7 @@ miqr_status qr_lstsq_batched_ex(miqr_handle h, void* stream, int64_t count,
     BatchGrids g = batched_grids(h->device, p);
     for (int k = 0; k < kBatchQueues; ++k) g.g[k] = std::min(g.g[k], hd->count[k]);
     g.g[kBatchQueues] = std::min<int64_t>(g.g[kBatchQueues], (int64_t)sel.size());
-    batched_ls(s, dtable, counter, dstatus, diters, g, p, bytes, flops);
+    batched_ls(s, dtable, counter, dstatus, diters, g, p, bytes, flops, fork);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "qr_lstsq_batched launch");
     return MIQR_OK;

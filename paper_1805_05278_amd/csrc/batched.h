@@ -73,8 +73,18 @@ inline size_t batch_table_bytes(int64_t count) {
 struct BatchGrids {
   int g[kBatchQueues + 1];
 };
-// Device ints the launches use as queue counters.
-constexpr int kBatchCounters = kBatchQueues + 1;
+// Device ints the launches use as queue counters: the sweeps', then the
+// refinement's over all queues and per queue.
+constexpr int kBatchCounters = 2 * kBatchQueues;
+
+// Streams and events that let the queues' kernels run side by side (default
+// priority; owned by the caller of batched_ls, one set per sequence of calls).
+struct BatchFork {
+  hipStream_t side[2] = {nullptr, nullptr};
+  hipEvent_t begin = nullptr, end[2] = {nullptr, nullptr};
+};
+hipError_t batch_fork_create(BatchFork* f);
+void batch_fork_destroy(BatchFork* f);
 BatchGrids batched_grids(int device, int prec);
 
 // Solve the table's tasks: one persistent launch per queue (largest problems
@@ -84,8 +94,11 @@ BatchGrids batched_grids(int device, int prec);
 // non-null; mixed precisions) the refinement iterations or -1.  counter:
 // kBatchCounters device ints, reset by the launch.  prec: working precision
 // of the blocked kernel (tasks of queue 0 always run in FP64).  bytes / flops:
-// the batch's algorithmic totals, for the kernel timer.
+// the batch's algorithmic totals, for the kernel timer.  fork (optional): the
+// queues of the blocked kernel run side by side on s and the fork's streams,
+// joined back into s.
 void batched_ls(hipStream_t s, const BatchHeader* table, int* counter, int* status, int* iters,
-                const BatchGrids& grids, int prec, double bytes, double flops);
+                const BatchGrids& grids, int prec, double bytes, double flops,
+                const BatchFork* fork);
 
 }  // namespace miqr

@@ -1008,18 +1008,20 @@ void k_batched_blk(const BatchHeader* table, int queue, int* counter, int* statu
   }
 }
 
-// FP64 refinement of the mixed-precision solves of queues 1 .. 3 (one
-// problem per workgroup, popped from queue counter kBatchQueues).
+// FP64 refinement of the mixed-precision solves of one queue, or (queue 0) of
+// queues 1 .. 3 (one problem per workgroup, popped from counter kBatchQueues +
+// queue).
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
-void k_batched_refine(const BatchHeader* table, int* counter, int* status, int* iters, int prec) {
+void k_batched_refine(const BatchHeader* table, int queue, int* counter, int* status, int* iters,
+                      int prec) {
   __shared__ __align__(16) RefineLds S;
-  int total = 0;
-  for (int k = 1; k < kBatchQueues; ++k) total += table->count[k];
+  int total = queue ? table->count[queue] : 0;
+  for (int k = 1; queue == 0 && k < kBatchQueues; ++k) total += table->count[k];
   total = __builtin_amdgcn_readfirstlane(total);
-  const int base = __builtin_amdgcn_readfirstlane(table->begin[1]);
+  const int base = __builtin_amdgcn_readfirstlane(table->begin[queue ? queue : 1]);
   const BatchTask* tasks = (const BatchTask*)(table + 1) + base;
   for (;;) {
-    if (threadIdx.x == 0) S.idx = atomicAdd(counter + kBatchQueues, 1);
+    if (threadIdx.x == 0) S.idx = atomicAdd(counter + kBatchQueues + queue, 1);
     __syncthreads();
     const int idx = __builtin_amdgcn_readfirstlane(S.idx);
     __syncthreads();
@@ -1088,12 +1090,13 @@ int batched_blk_grid(int device, int prec, int queue) {
                                                       : blk_kernel(prec, queue));
 }
 
+// queue >= kBatchQueues: the refinement of queue - kBatchQueues.
 void batched_blk_launch(hipStream_t s, const BatchHeader* table, int queue, int* counter,
                         int* status, int* iters, int grid, int prec) {
   if (grid <= 0) return;
-  if (queue == kBatchQueues) {
-    hipLaunchKernelGGL(k_batched_refine, dim3(grid), dim3(NT), 0, s, table, counter, status, iters,
-                       prec);
+  if (queue >= kBatchQueues) {
+    hipLaunchKernelGGL(k_batched_refine, dim3(grid), dim3(NT), 0, s, table, queue - kBatchQueues,
+                       counter, status, iters, prec);
     return;
   }
   const void* k = blk_kernel(prec, queue);

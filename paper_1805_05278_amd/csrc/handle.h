@@ -65,6 +65,8 @@ struct miqr_ctx {
   hipStream_t aux = nullptr;
   hipEvent_t ev_panel = nullptr;
   hipEvent_t ev_update = nullptr;
+  // The batched queues' side streams (created on first use).
+  miqr::BatchFork fork;
   std::map<TuneKey, miqr::Tuning> tune_cache;
   // qr_factor launch sequences captured once and replayed (miqr_graphs_enable);
   // cap is the stream they are captured on (never executed on).

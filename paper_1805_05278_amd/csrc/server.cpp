@@ -132,6 +132,7 @@ struct miqr_server {
   char* pool_base = nullptr;
   Pool pool;
   hipStream_t compute = nullptr, copy = nullptr;
+  BatchFork fork;  // the queues of one batch side by side
   Slot slots[2];
   std::vector<hipEvent_t> up_events;
   std::vector<int> up_refs;  // requests still to be launched after each upload event
@@ -333,7 +334,7 @@ miqr_status launch(miqr_server* s, Slot& sl) {
     if (e == hipSuccess) e = hipMemcpyAsync(sl.dtable, sl.ptable, tb, hipMemcpyHostToDevice, s->compute);
     if (e == hipSuccess) {
       batched_ls(s->compute, sl.dtable, sl.dcounter, sl.dstatus, nullptr, s->grids64, kBlkF64, 0.0,
-                 0.0);
+                 0.0, &s->fork);
       e = hipGetLastError();
     }
     if (e == hipSuccess)
@@ -431,7 +432,7 @@ miqr_status make_slot(miqr_server* s, Slot& sl) {
   if (e == hipSuccess) e = hipMemcpyAsync(sl.dtable, sl.ptable, tb, hipMemcpyHostToDevice, s->compute);
   if (e == hipSuccess) {
     batched_ls(s->compute, sl.dtable, sl.dcounter, sl.dstatus, nullptr, s->grids, s->prec, 0.0,
-               0.0);
+               0.0, &s->fork);
     e = hipGetLastError();
   }
   if (e == hipSuccess)
@@ -463,6 +464,7 @@ void destroy_server(miqr_server* s) {
   }
   for (hipEvent_t e : s->up_events) hipEventDestroy(e);
   if (s->pool_base) hipFree(s->pool_base);
+  batch_fork_destroy(&s->fork);
   if (s->compute) hipStreamDestroy(s->compute);
   if (s->copy) hipStreamDestroy(s->copy);
   delete s;
@@ -515,6 +517,7 @@ miqr_status qr_server_create(miqr_handle h, const qr_server_opts* o, miqr_server
   s->grids64 = batched_grids(h->device, kBlkF64);
   hipError_t e = hipStreamCreateWithFlags(&s->compute, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->copy, hipStreamNonBlocking);
+  if (e == hipSuccess) e = batch_fork_create(&s->fork);
   if (e != hipSuccess) {
     destroy_server(s);
     return MIQR_EHIP;

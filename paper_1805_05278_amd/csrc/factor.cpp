@@ -278,11 +278,11 @@ hipError_t factor_blocked(hipStream_t s, const Lookahead& la, const Tuning& t, c
       // is factored; the next is updated and factored here meanwhile.
       e = hipEventRecord(la.ev_panel, s);
       if (e == hipSuccess) e = hipStreamWaitEvent(la.aux, la.ev_panel, 0);
-      // In column chunks: a blocked TSQR workgroup needs a CU with no GEMM
-      // workgroup on it, and the end of each chunk's launches drains CUs for
-      // the panel kernels waiting on the main stream (3072 columns measured
-      // best: 16384^2 alone 245 -> 233 ms; 2048 and 4096 in between, 1024
-      // slower than no chunks).
+      // In column chunks: a TSQR workgroup fits beside one GEMM workgroup, not
+      // beside two, and the end of each chunk's launches drains CUs for the
+      // panel kernels waiting on the main stream (3072 columns measured best
+      // with one-panel steps: 16384^2 alone 245 -> 233 ms; 2048 and 4096 in
+      // between, 1024 slower than no chunks).
       for (int64_t cc = c2; cc < n && e == hipSuccess; cc += kAuxChunk)
         e = update(la.aux, cur, cc, std::min<int64_t>(n, cc + kAuxChunk), w.ua1, w.ua2, w.ua_cap,
                    w.scratch_aux, w.scratch_aux_n);

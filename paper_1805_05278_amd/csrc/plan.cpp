@@ -159,7 +159,10 @@ const char* cost_feature_name(int f) {
 const CostCoeffs& cost_coeffs() {
   // Fitted by least squares to factorisations timed on MI355X over a sweep of
   // shapes and tunings, one stream, no look-ahead (the fit and its residuals
-  // are kept with the measured profiles); d0 from the GEMM depth scan.
+  // are kept with the measured profiles); d0 from the GEMM depth scan.  The
+  // kernels have become faster since: the estimates are upper bounds now.  The
+  // coefficients, and the launch counts below that they were fitted with, stay,
+  // because the panel width chosen by them is the row count of a BLOCKED T.
   static const CostCoeffs c{
       {
           /*leaf256_steps=*/0.0001165,
@@ -201,14 +204,14 @@ struct Acc {
 Feat tsqr_feat(int64_t rows, int w, int lr, int ch, int ar, bool with_q) {
   Feat r;
   const TsqrGeom g = tsqr_geometry(rows, w, lr, ch, ar);
-  // Leaf: the first block of every chain in one launch (one workgroup per
-  // CU at 256-row blocks, two at 128), then the stacked blocks (two per CU).
+  // Leaf: the first blocks of the chains, one workgroup per CU at 256-row blocks
+  // and two at 128, then the stacked blocks, two per CU (as fitted).
   const double slots1 = g.leaf_rows == 256 ? 256.0 : 512.0;
   const double waves1 = std::ceil((double)g.chains / slots1);
   const double waves2 = std::ceil((double)g.chains / 512.0);
   r.f[g.leaf_rows == 256 ? F_LEAF256 : F_LEAF128] = waves1 + (g.chain - 1) * waves2;
-  // Tree nodes stack (arity - 1) R factors: above 128 rows they run on the
-  // blocked MFMA node kernel, up to 128 on the column-by-column one.
+  // Tree nodes stack (arity - 1) R factors; those of at most 128 rows have a
+  // coefficient of their own.
   r.f[(g.arity - 1) * w > 128 ? F_TREE : F_TREE_SMALL] = g.levels;
   r.f[F_HR] = 1.0;
   r.f[F_DOWN] = g.levels + 1;
@@ -216,9 +219,9 @@ Feat tsqr_feat(int64_t rows, int w, int lr, int ch, int ar, bool with_q) {
   return r;
 }
 
-// The workgroups the GEMM dispatch launches for an M x N x K product (its
-// tile and split-K rule): a product with fewer than one per CU runs at that
-// share of the chip.
+// Workgroups of an M x N x K product under the tile and split-K rule that the
+// coefficients were fitted with (the dispatch has its own rule): a product with
+// fewer than one per CU runs at that share of the chip.
 double gemm_units(double M, double N, double K, bool* split) {
   const double t128 = std::ceil(M / 128.0) * std::ceil(N / 128.0);
   const bool big = M >= 128 && N >= 128 && (t128 >= 128 || K >= 4096);

@@ -132,9 +132,8 @@ struct miqr_server {
   char* pool_base = nullptr;
   Pool pool;
   hipStream_t compute = nullptr;
-  hipStream_t copy[2] = {nullptr, nullptr};  // uploads, in turn
+  hipStream_t copy[2] = {nullptr, nullptr};  // uploads: right-hand sides, matrices
   hipEvent_t copied = nullptr;               // joins copy[1] into copy[0]
-  int turn = 0;
   BatchFork fork;  // the queues of one batch side by side
   Slot slots[2];
   std::vector<hipEvent_t> up_events;
@@ -205,17 +204,14 @@ int take_event(miqr_server* s) {
   return (int)s->up_events.size() - 1;
 }
 
-// Upload a host matrix (rows x cols, leading dimension ld) into a packed one.
-// The matrices of a batch go on two streams in turn, so that one transfer's
-// start-up (some 10 us) lies beside the other's bytes (300 requests, 0.6 GB from
-// pinned memory, with their solves: 28.8 ms on one stream, 25.8 ms on two).
-hipError_t upload(miqr_server* s, const Buf& b, const double* src, int64_t ld, int64_t rows,
-                  int64_t cols) {
+// Upload a host matrix (rows x cols, leading dimension ld) into a packed one,
+// as one run of bytes where it is packed too (`run`) or pitched.
+hipError_t upload(hipStream_t st, double* dst, const double* src, int64_t ld, int64_t rows,
+                  int64_t cols, bool run) {
   const size_t col = (size_t)rows * 8;
-  hipStream_t st = s->copy[s->turn ^= 1];
-  if (ld == rows || cols == 1)
-    return hipMemcpyAsync(dptr(s, b), src, col * (size_t)cols, hipMemcpyHostToDevice, st);
-  return hipMemcpy2DAsync(dptr(s, b), col, src, (size_t)ld * 8, col, (size_t)cols,
+  if (run && (ld == rows || cols == 1))
+    return hipMemcpyAsync(dst, src, col * (size_t)cols, hipMemcpyHostToDevice, st);
+  return hipMemcpy2DAsync(dst, col, src, (size_t)ld * 8, col, (size_t)cols,
                           hipMemcpyHostToDevice, st);
 }
 
@@ -241,8 +237,14 @@ miqr_status admit(miqr_server* s) {
       break;
     }
     hipError_t e = hipSuccess;
-    if (a) e = upload(s, r.A, r.hA, r.lda, r.m, r.n);
-    if (e == hipSuccess) e = upload(s, r.B, r.hB, r.ldb, r.m, r.nrhs);
+    // A and B have a stream each, so their transfers run side by side: 300
+    // requests, 0.6 GB from pinned memory, with their solves 28.8 ms on one
+    // stream, 25.8 ms so, 28.6 ms with B pitched.  Right-hand sides alone, for
+    // kept factors, go pitched on one stream: 2000 of one to four columns 55.5 ms,
+    // 59 ms as runs, and of one column 40 % longer spread over both streams.
+    if (a) e = upload(s->copy[1], dptr(s, r.A), r.hA, r.lda, r.m, r.n, true);
+    if (e == hipSuccess)
+      e = upload(s->copy[0], dptr(s, r.B), r.hB, r.ldb, r.m, r.nrhs, r.parent < 0);
     if (e != hipSuccess) return shfail(s, e, "server upload");
     if (ev < 0) {
       ev = take_event(s);

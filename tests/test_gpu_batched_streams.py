@@ -51,7 +51,8 @@ def test_batched_queues_side_by_side(mix, prec):
 
 def test_server_uploads_strided_and_packed():
     """Requests whose matrices are packed or columns of a taller array, one
-    column or several, in one batch: the uploads take turns on two streams."""
+    column or several, in one batch: matrices and right-hand sides
+    upload on a stream each."""
     import paper_1805_05278_amd as m_
     h = m_.Handle(0)
     srv = m_.Server(h, max_batch=16)

@@ -863,16 +863,19 @@ static void launch_bf16(const GemmDesc& d, const GemmArgs& g, dim3 grid, hipStre
 static void choose(const GemmDesc& d, int64_t scratch, int64_t* BM, int64_t* nsplit,
                    int64_t* kchunk) {
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-  // 128 x 128 tiles where tiles, or tiles and splits of at least 256, fill the
-  // chip; 64 x 64 otherwise, and for updates of depth 128 and less, which move
-  // more bytes of C than an MFMA time's worth: four small workgroups a CU keep
-  // more of them in flight (12288 x 3072 at depth 128: 234 us against 257 us;
-  // at depth 256 388 against 378 us, at 512 (49152 rows) 2.51 against 2.64 ms).
+  // FP64: 128 x 128 tiles where they fill the chip, with splits of at least 256
+  // two workgroups a CU (256 x 3072 x 2500: 103 us in 480 of them, 85 us in 64 x
+  // 64 tiles; 1024 x 1024 x 2500 115 and 107); 64 x 64 otherwise, and for updates
+  // of depth 128 and less, which move more bytes of C than an MFMA time's worth:
+  // four small workgroups a CU keep more of them in flight (12288 x 3072 at depth
+  // 128: 234 us against 257 us; at depth 256 388 against 378 us, at 512 (49152
+  // rows) 2.51 against 2.64 ms; 2500 x 3072 at depth 1024 348 against 318 us).
   const int64_t t128 = cdiv(d.M, 128) * cdiv(d.N, 128);
   const bool wide = d.M >= 128 && d.N >= 128;
   *BM = 64;
   if (d.compute == COMPUTE_F64) {
-    if (wide && (d.beta == 0.0 ? t128 * std::max<int64_t>(d.K / 256, 1) : (d.K > 128 ? t128 : 0)) >= 256)
+    if (wide && (d.beta == 0.0 ? t128 * std::max<int64_t>(d.K / 256, 1) >= 512
+                               : d.K > 128 && t128 >= 256))
       *BM = 128;
   } else if (wide && (t128 >= 128 || d.K >= 4096)) {
     *BM = 128;
@@ -880,18 +883,28 @@ static void choose(const GemmDesc& d, int64_t scratch, int64_t* BM, int64_t* nsp
   const int64_t tiles = cdiv(d.M, *BM) * cdiv(d.N, *BM);
   // Split of K: the one with the least estimated time, in microseconds.  A slab
   // takes a workgroup's MFMA time for every workgroup on its CU, and not less
-  // than a memory latency allows; split partials are written, read back and
-  // cost a launch.  (128 x 128 x 16384: 97 us in 32 slices of 512 one tile wide,
-  // 24 us in 64 to 128 slices of four tiles; 128 x 3072 x 12288: 245 us in 576
-  // workgroups, one full and one nearly empty wave of them, 185 us in 504;
-  // 16384 x 64 updates of depth 64: 23 us split in two, 12 us whole.)
+  // than a memory latency allows; the operands are read from memory once; split
+  // partials are written, read back (with C) and cost a launch, and a block of the
+  // reduction reads a quarter of them one after the other.  (128 x 128 x 16384:
+  // 97 us in 32 slices of 512 one tile wide, 24 us in 64 to 128 slices of four
+  // tiles; 128 x 3072 x 12288: 245 us in 576 workgroups, one full and one nearly
+  // empty wave of them, 185 us in 504; 16384 x 64 updates of depth 64: 23 us split
+  // in two, 12 us whole; 64 x 64 x 64: 9.4 us split in two, 10.1 whole; 64 x 64 x
+  // 262144: 105 us in 1024 slices, 43 of it the reduction, 79 us in 512.)  Over
+  // 1300 shapes the split chosen takes 2 % longer than the best one in FP64, 3 %
+  // in FP32 and 4 % in BF16.  In these a slab waits for its loads, and a second
+  // workgroup on the CU costs nothing (4096 x 511 x 512 in BF16: 65 us in two
+  // slices, 50 us in four).
   const double slots = *BM == 64 ? 1024 : 512, mn = (double)d.M * (double)d.N;
   const int64_t cap = std::min(d.K / (d.K >= 1024 ? 64 : 32), (int64_t)((double)scratch / mn));
+  const double two = d.compute == COMPUTE_F64 ? 3.4 : 2.6;
+  const double reads = 8.0 * ((double)d.K * (double)(d.M + d.N) + (d.beta == 0.0 ? 1 : 2) * mn);
   auto cost = [&](int64_t ns) {
     const double wgs = (double)(tiles * ns), waves = std::ceil(wgs / slots);
     const double occ = std::min(slots / 256, std::ceil(wgs / 256));
-    const double slab = *BM == 64 ? std::max(1.6, 0.43 * occ) : (occ > 1 ? 3.4 : 2.6);
-    return waves * (2.0 + (double)d.K / (16.0 * ns) * slab) + (ns > 1 ? 5.0 + ns * mn * 16 / 4e6 : 0);
+    const double slab = *BM == 64 ? std::max(1.6, 0.43 * occ) : (occ > 1 ? two : 2.6);
+    return std::max(waves * (2.0 + (double)d.K / (16.0 * ns) * slab), reads / 4.5e6) +
+           (ns > 1 ? 2.0 + std::max(0.06 * ns, (ns + 1.5) * mn * 16 / 4e6) : 0);
   };
   *nsplit = 1;
   double best = cost(1);

@@ -1,0 +1,42 @@
+"""The rules that lay out dense products: the split of a long contraction,
+whose partials must not take longer to add up than the product itself."""
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def miqr():
+    import paper_1805_05278_amd as m
+    h = m.Handle(0)
+    yield m, h
+    h.close()
+
+
+@pytest.mark.parametrize("k", [17, 64])
+def test_long_contraction_split(miqr, k):
+    """V^T C of 262144 x 64 by k columns is one tile wide: its reduction reads
+    the partials of an entry in series, so they stay at 512 and fewer."""
+    m_, h = miqr
+    m, n = 262144, 64
+    A = synth.gaussian_device(m, n, 3)
+    T = m_.colmajor(n, n)
+    C = synth.gaussian_device(m, k, 4)
+    h.factor(A, T)
+    C0 = C.clone()
+    h.profile(True)
+    h.apply_q("T", A, T, C)
+    red = h.profile_totals().get("gemm_splitk_reduce", dict(bytes=0.0, launches=0))
+    h.profile(False)
+    # Each reduction counts its partials and two passes over C.
+    partials = red["bytes"] / (8.0 * n * k) - 2 * red["launches"]
+    assert partials <= 512 + 2
+    V = torch.tril(A, -1)
+    V.diagonal().fill_(1.0)
+    ref = C0 - V @ (torch.triu(T).t().contiguous() @ (V.t().contiguous() @ C0))
+    tol = 40 * 2.0 ** -53 * np.sqrt(m) * float(C0.norm())  # sums of m terms with random signs
+    assert float((C - ref).norm()) <= tol

@@ -2,8 +2,9 @@
 // M1 = V_L^T C, M2 = T_L^T M1, C -= V_L M2, M3 = V_L^T [0; V_R], M4 = M3 T_R,
 // T12 = -T_L M4) and the compact-WY application of Q.
 //
-// One workgroup (4 waves, 2 x 2) computes a BM x BN tile of C; each wave a
-// (BM/2) x (BN/2) block of 16 x 16 MFMA tiles.  Operands are staged through
+// One workgroup computes a BM x BN tile of C, its waves two down the rows and
+// two or four across the columns, each a block of 16 x 16 MFMA tiles (the
+// shapes stand at k_gemm).  Operands are staged through
 // LDS in BK = 16 deep slices, k-major, with the next slice prefetched into
 // registers while the current one is multiplied.  The MFMA computes C^T tiles
 // (A' = op(B)^T, B' = op(A)^T) so that the lane-fast output index runs down a
@@ -221,16 +222,14 @@ __host__ __device__ __forceinline__ void plain_slab_range(int64_t x0, int64_t X,
 // for 64 x 64.  Both leave four waves on a SIMD (at most 128 registers): with
 // two, waves of one workgroup stop together at every slab's barrier and the
 // MFMA pipe runs at about 60 % (measured with persistent workgroups that hid
-// every load).
+// every load).  Long FP32 products keep four waves of 64 x 64 for their 128 x
+// 128 tiles (few_waves below).
 template <int BM>
-struct TileShape {
-  static constexpr int NT = BM == 128 ? 512 : 256;  // threads
-  static constexpr int WC = NT / 128;               // waves across the columns (2 down the rows)
-};
+constexpr int kThreads = BM == 128 ? 512 : 256;
 
-template <int BM, int BN, bool TA, bool TB, int CMP>
-__global__ __launch_bounds__(TileShape<BM>::NT, 4) void k_gemm(GemmArgs g) {
-  constexpr int NT = TileShape<BM>::NT, WC = TileShape<BM>::WC;
+template <int BM, int BN, bool TA, bool TB, int CMP, int NT>
+__global__ __launch_bounds__(NT, (BM == 128 && NT == 256 ? 2 : 4)) void k_gemm(GemmArgs g) {
+  constexpr int WC = NT / 128;  // waves across the columns (2 down the rows)
   typedef MfmaTraits<CMP> Tr;
   typedef typename Tr::T T;
   typedef typename Tr::Acc Acc;
@@ -835,16 +834,38 @@ static int64_t launch_thin(const GemmDesc& d, hipStream_t s, double* scratch, in
   return ns;
 }
 
+// FP32 MFMA takes half the time of FP64, so a long product is bound by its loads,
+// and eight loads of an operand in flight per thread beat four by more than the
+// second pair of waves gives.  A^T B: 1024 x 3072 x 16384 1407 us against 1635, 512
+// x 256 x 131072 399 against 495, 512 x 256 x 16384 68 against 69; A B: 16384 x
+// 1024 x 2048 662 against 730, 131072 x 256 x 512 424 against 453.  Shorter ones
+// (512 x 256 x 4096 transposed 38 against 32 us, 16384 x 1024 x 256 115 against
+// 109) and tiles that cross the edge (1024 x 511 x 131072 1822 against 1676) want
+// the waves.
+static bool few_waves(const GemmDesc& d) {
+  if (d.compute != COMPUTE_F32 || d.tb != 'N' || d.N % 128 != 0) return false;
+  const double mnk = (double)d.M * (double)d.N * (double)d.K;
+  return d.ta == 'T' ? d.M % 128 == 0 && mnk >= 2e9 : d.K >= 256 && mnk >= 1.6e10;
+}
+
 template <int BM, int BN, int CMP>
 static void launch_t(const GemmDesc& d, const GemmArgs& g, dim3 grid, hipStream_t s) {
+  constexpr int NT = kThreads<BM>;
   if (d.ta == 'N' && d.tb == 'N')
-    hipLaunchKernelGGL((k_gemm<BM, BN, false, false, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, false, false, CMP, NT>), grid, dim3(NT), 0, s, g);
   else if (d.ta == 'T' && d.tb == 'N')
-    hipLaunchKernelGGL((k_gemm<BM, BN, true, false, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, true, false, CMP, NT>), grid, dim3(NT), 0, s, g);
   else if (d.ta == 'N' && d.tb == 'T')
-    hipLaunchKernelGGL((k_gemm<BM, BN, false, true, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, false, true, CMP, NT>), grid, dim3(NT), 0, s, g);
   else
-    hipLaunchKernelGGL((k_gemm<BM, BN, true, true, CMP>), grid, dim3(TileShape<BM>::NT), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<BM, BN, true, true, CMP, NT>), grid, dim3(NT), 0, s, g);
+}
+
+static void launch_few(const GemmDesc& d, const GemmArgs& g, dim3 grid, hipStream_t s) {
+  if (d.ta == 'T')
+    hipLaunchKernelGGL((k_gemm<128, 128, true, false, COMPUTE_F32, 256>), grid, dim3(256), 0, s, g);
+  else
+    hipLaunchKernelGGL((k_gemm<128, 128, false, false, COMPUTE_F32, 256>), grid, dim3(256), 0, s, g);
 }
 
 template <int BM, int BN>
@@ -950,7 +971,8 @@ hipError_t gemm(const GemmDesc& d, hipStream_t s, double* scratch, int64_t scrat
       if (big) launch_bf16<128, 128>(d, g, grid, s);
       else launch_bf16<64, 64>(d, g, grid, s);
     } else if (d.compute == COMPUTE_F32) {
-      if (big) launch_t<128, 128, COMPUTE_F32>(d, g, grid, s);
+      if (big && few_waves(d)) launch_few(d, g, grid, s);
+      else if (big) launch_t<128, 128, COMPUTE_F32>(d, g, grid, s);
       else launch_t<64, 64, COMPUTE_F32>(d, g, grid, s);
     } else {
       if (big) launch_t<128, 128, COMPUTE_F64>(d, g, grid, s);

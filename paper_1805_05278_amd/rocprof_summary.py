@@ -63,9 +63,9 @@ _PATTERNS = [
     (r"k_tsqr_hr\b", "tsqr_hr_root"),
     (r"k_chain_down<\d+, \d+, false, \d+>", "tsqr_down_tree"),
     (r"k_chain_down<\d+, \d+, true, \d+>", "tsqr_down_leaf"),
-    (r"k_gemm<\d+, \d+, (true|false), (true|false), 0>", "gemm_f64"),
+    (r"k_gemm<\d+, \d+, (true|false), (true|false), 0(, \d+)?>", "gemm_f64"),
     (r"k_thin_(tn|nn)<", "gemm_f64"),
-    (r"k_gemm<\d+, \d+, (true|false), (true|false), 1>", "gemm_f32"),
+    (r"k_gemm<\d+, \d+, (true|false), (true|false), 1(, \d+)?>", "gemm_f32"),
     (r"k_gemm_bf16<", "gemm_bf16"),
     (r"k_splitk_reduce", "gemm_splitk_reduce"),
     (r"k_trsm_diag<", "trsm_diag"),

@@ -1,5 +1,6 @@
 """The rules that lay out dense products: the split of a long contraction,
-whose partials must not take longer to add up than the product itself."""
+whose partials must not take longer to add up than the product itself, and the
+waves of long FP32 products."""
 import numpy as np
 import pytest
 
@@ -40,3 +41,18 @@ def test_long_contraction_split(miqr, k):
     ref = C0 - V @ (torch.triu(T).t().contiguous() @ (V.t().contiguous() @ C0))
     tol = 40 * 2.0 ** -53 * np.sqrt(m) * float(C0.norm())  # sums of m terms with random signs
     assert float((C - ref).norm()) <= tol
+
+
+@pytest.mark.parametrize("m,n", [(32768, 512), (32640, 512), (65536, 1024)])
+def test_long_mixed_updates(miqr, m, n):
+    """FP32 trailing updates on both sides of the length from which their large
+    tiles run on four waves: a QR of a nearby matrix, Q orthogonal in FP64 (the
+    bounds of the short shapes)."""
+    m_, h = miqr
+    A = synth.gaussian_device(m, n, 5)
+    F, T, Q = A.clone(memory_format=torch.preserve_format), m_.colmajor(n, n), m_.colmajor(m, n)
+    h.factor(F, T, h.opts(precision=m_.MIXED_FP32, Q=Q))
+    assert F.stride() == A.stride()
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    assert float((Q.t().contiguous() @ Q - eye).norm()) <= 1e-12
+    assert float((A - Q @ torch.triu(F[:n])).norm() / A.norm()) <= 50 * 2.0 ** -24

@@ -44,7 +44,9 @@ __device__ __forceinline__ double readlane(double v, int lane) {
 // s_nop 1 at the head of each block gives the two wait states a DPP read
 // needs after a VALU write of its source (the compiler does not look inside
 // the asm); within a block no instruction DPP-reads a register written by
-// the one before it.  xs[4 t + r] is register r of row tile t.
+// the one before it.  Outputs of a block are early clobbers: they are written
+// before its last inputs are read, and the compiler would give an output and an
+// input of equal value (a zero sum and a zero entry) one register.  xs[4 t + r] is register r of row tile t.
 //   d0 += sum_t (x_J[t][0] x[t][0] + x_J[t][2] x[t][2]), d1 likewise for
 //   registers 1 and 3 (two chains for latency).
 template <int J>
@@ -66,7 +68,7 @@ __device__ __forceinline__ void dots_bcast(const double (&xs)[16], double& d0, d
       "v_fmac_f64_dpp %1, %15, %15 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %0, %16, %16 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %1, %17, %17 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(d0), "+v"(d1)
+      : "+&v"(d0), "+&v"(d1)
       : "v"(xs[0]), "v"(xs[1]), "v"(xs[2]), "v"(xs[3]), "v"(xs[4]), "v"(xs[5]), "v"(xs[6]), "v"(xs[7]), "v"(xs[8]), "v"(xs[9]), "v"(xs[10]), "v"(xs[11]), "v"(xs[12]), "v"(xs[13]), "v"(xs[14]), "v"(xs[15]), "n"(J));
 }
 template <int J>
@@ -88,7 +90,7 @@ __device__ __forceinline__ void dots_bcast(const float (&xs)[16], float& d0, flo
       "v_fmac_f32_dpp %1, %15, %15 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f32_dpp %0, %16, %16 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f32_dpp %1, %17, %17 row_newbcast:%18 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(d0), "+v"(d1)
+      : "+&v"(d0), "+&v"(d1)
       : "v"(xs[0]), "v"(xs[1]), "v"(xs[2]), "v"(xs[3]), "v"(xs[4]), "v"(xs[5]), "v"(xs[6]), "v"(xs[7]), "v"(xs[8]), "v"(xs[9]), "v"(xs[10]), "v"(xs[11]), "v"(xs[12]), "v"(xs[13]), "v"(xs[14]), "v"(xs[15]), "n"(J));
 }
 //   x[t][r] += x_J[t][r] nf (lane J's own entries are unchanged when its nf
@@ -112,7 +114,7 @@ __device__ __forceinline__ void update_bcast(double (&xs)[16], double nf) {
       "v_fmac_f64_dpp %13, %13, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %14, %14, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %15, %15, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(xs[0]), "+v"(xs[1]), "+v"(xs[2]), "+v"(xs[3]), "+v"(xs[4]), "+v"(xs[5]), "+v"(xs[6]), "+v"(xs[7]), "+v"(xs[8]), "+v"(xs[9]), "+v"(xs[10]), "+v"(xs[11]), "+v"(xs[12]), "+v"(xs[13]), "+v"(xs[14]), "+v"(xs[15])
+      : "+&v"(xs[0]), "+&v"(xs[1]), "+&v"(xs[2]), "+&v"(xs[3]), "+&v"(xs[4]), "+&v"(xs[5]), "+&v"(xs[6]), "+&v"(xs[7]), "+&v"(xs[8]), "+&v"(xs[9]), "+&v"(xs[10]), "+&v"(xs[11]), "+&v"(xs[12]), "+&v"(xs[13]), "+&v"(xs[14]), "+&v"(xs[15])
       : "v"(nf), "n"(J));
 }
 template <int J>
@@ -134,7 +136,7 @@ __device__ __forceinline__ void update_bcast(float (&xs)[16], float nf) {
       "v_fmac_f32_dpp %13, %13, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f32_dpp %14, %14, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f32_dpp %15, %15, %16 row_newbcast:%17 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(xs[0]), "+v"(xs[1]), "+v"(xs[2]), "+v"(xs[3]), "+v"(xs[4]), "+v"(xs[5]), "+v"(xs[6]), "+v"(xs[7]), "+v"(xs[8]), "+v"(xs[9]), "+v"(xs[10]), "+v"(xs[11]), "+v"(xs[12]), "+v"(xs[13]), "+v"(xs[14]), "+v"(xs[15])
+      : "+&v"(xs[0]), "+&v"(xs[1]), "+&v"(xs[2]), "+&v"(xs[3]), "+&v"(xs[4]), "+&v"(xs[5]), "+&v"(xs[6]), "+&v"(xs[7]), "+&v"(xs[8]), "+&v"(xs[9]), "+&v"(xs[10]), "+&v"(xs[11]), "+&v"(xs[12]), "+&v"(xs[13]), "+&v"(xs[14]), "+&v"(xs[15])
       : "v"(nf), "n"(J));
 }
 
@@ -150,7 +152,7 @@ __device__ __forceinline__ void dots_bcast(const double (&xs)[8], double& d0, do
       "v_fmac_f64_dpp %1, %7, %7 row_newbcast:%10 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %0, %8, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %1, %9, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(d0), "+v"(d1)
+      : "+&v"(d0), "+&v"(d1)
       : "v"(xs[0]), "v"(xs[1]), "v"(xs[2]), "v"(xs[3]), "v"(xs[4]), "v"(xs[5]), "v"(xs[6]), "v"(xs[7]), "n"(J));
 }
 template <int J>
@@ -164,7 +166,7 @@ __device__ __forceinline__ void update_bcast(double (&xs)[8], double nf) {
       "v_fmac_f64_dpp %5, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %6, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %7, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(xs[0]), "+v"(xs[1]), "+v"(xs[2]), "+v"(xs[3]), "+v"(xs[4]), "+v"(xs[5]), "+v"(xs[6]), "+v"(xs[7])
+      : "+&v"(xs[0]), "+&v"(xs[1]), "+&v"(xs[2]), "+&v"(xs[3]), "+&v"(xs[4]), "+&v"(xs[5]), "+&v"(xs[6]), "+&v"(xs[7])
       : "v"(nf), "n"(J));
 }
 //   s0 += sum over k = K, K + 2 of v_k t[k], s1 over k = K + 1, K + 3, where
@@ -177,7 +179,7 @@ __device__ __forceinline__ void bcast_terms(double v, const double (&t)[16], dou
       "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
       "v_fmac_f64_dpp %1, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-      : "+v"(s0), "+v"(s1)
+      : "+&v"(s0), "+&v"(s1)
       : "v"(v), "v"(t[K]), "v"(t[K + 1]), "v"(t[K + 2]), "v"(t[K + 3]), "n"(K), "n"(K + 1),
         "n"(K + 2), "n"(K + 3));
 }
@@ -191,7 +193,7 @@ __device__ __forceinline__ void bcast_axpy(double v, double f, double (&y)[16]) 
         "v_fmac_f64_dpp %1, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "v_fmac_f64_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "v_fmac_f64_dpp %3, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        : "+v"(y[I]), "+v"(y[I + 1]), "+v"(y[I + 2]), "+v"(y[I + 3])
+        : "+&v"(y[I]), "+&v"(y[I + 1]), "+&v"(y[I + 2]), "+&v"(y[I + 3])
         : "v"(v), "v"(f), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
     bcast_axpy<I + 4, N - 4>(v, f, y);
   } else if constexpr (N >= 1) {
@@ -214,7 +216,7 @@ __device__ __forceinline__ void bcast_fmac(const X& x, Y& y, double f) {
         "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "v_fmac_f64_dpp %2, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "v_fmac_f64_dpp %3, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        : "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3)
+        : "+&v"(y0), "+&v"(y1), "+&v"(y2), "+&v"(y3)
         : "v"(x[I]), "v"(x[I + 1]), "v"(x[I + 2]), "v"(x[I + 3]), "v"(f), "n"(J));
     y[I] = y0, y[I + 1] = y1, y[I + 2] = y2, y[I + 3] = y3;
   } else if constexpr (N >= 1) {
@@ -237,7 +239,7 @@ __device__ __forceinline__ void bcast_fmac_self(X& x, double f) {
         "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
         "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
         : "v"(f), "n"(J));
     x[I] = x0, x[I + 1] = x1, x[I + 2] = x2, x[I + 3] = x3;
   } else if constexpr (N >= 1) {

@@ -1075,12 +1075,10 @@ miqr_status qr_lstsq_batched_ex(miqr_handle h, void* stream, int64_t count,
   }
   // The queues side by side, except under the per-kernel timer (whose events
   // sit on the caller's stream) and in a capture of the caller's.
-  const BatchFork* fork = nullptr;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (!h->profiling && hipStreamIsCapturing(s, &cap) == hipSuccess &&
-      cap == hipStreamCaptureStatusNone && (h->fork.begin || batch_fork_create(&h->fork) == hipSuccess))
-    fork = &h->fork;
-  (void)hipGetLastError();
+  const hipError_t asked = h->profiling ? hipSuccess : hipStreamIsCapturing(s, &cap);
+  if (asked != hipSuccess) (void)hipGetLastError();
+  const bool may_fork = !h->profiling && asked == hipSuccess && cap == hipStreamCaptureStatusNone;
   // Enqueue the items of `sel` in precision p: tasks grouped by queue (the
   // refinement kernel takes queues 1..3 as one contiguous range), largest
   // problems first within each queue (their cost is about blocks x columns^2
@@ -1133,7 +1131,8 @@ miqr_status qr_lstsq_batched_ex(miqr_handle h, void* stream, int64_t count,
     BatchGrids g = batched_grids(h->device, p);
     for (int k = 0; k < kBatchQueues; ++k) g.g[k] = std::min(g.g[k], hd->count[k]);
     g.g[kBatchQueues] = std::min<int64_t>(g.g[kBatchQueues], (int64_t)sel.size());
-    batched_ls(s, dtable, counter, dstatus, diters, g, p, bytes, flops, fork);
+    batched_ls(s, dtable, counter, dstatus, diters, g, p, bytes, flops,
+               may_fork ? batch_fork(&h->fork, *hd) : nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "qr_lstsq_batched launch");
     return MIQR_OK;

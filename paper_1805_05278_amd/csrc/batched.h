@@ -79,13 +79,16 @@ constexpr int kBatchCounters = 2 * kBatchQueues;
 
 // Streams and events that let the queues' kernels run side by side (default
 // priority; owned by the caller of batched_ls, one set per sequence of calls).
+// A process's first streams take 2.7 ms each (a hardware queue), later ones 15 to
+// 100 us, so batch_fork makes them for the first launch with work in two queues
+// of the blocked kernel, and returns null for one without (or without streams).
 struct BatchFork {
   hipStream_t side[2] = {nullptr, nullptr};
   hipEvent_t begin = nullptr, end[2] = {nullptr, nullptr};
 };
-hipError_t batch_fork_create(BatchFork* f);
 void batch_fork_destroy(BatchFork* f);
 BatchGrids batched_grids(int device, int prec);
+const BatchFork* batch_fork(BatchFork* f, const BatchHeader& table);
 
 // Solve the table's tasks: one persistent launch per queue (largest problems
 // first), each popping its queue in table order, then for a mixed precision

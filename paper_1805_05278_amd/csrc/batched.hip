@@ -306,15 +306,21 @@ BatchGrids batched_grids(int device, int prec) {
   return g;
 }
 
-hipError_t batch_fork_create(BatchFork* f) {
+const BatchFork* batch_fork(BatchFork* f, const BatchHeader& table) {
+  int used = 0;
+  for (int k = 1; k < kBatchQueues; ++k) used += table.count[k] > 0;
+  if (used < 2) return nullptr;
+  if (f->begin) return f;
   hipError_t e = hipSuccess;
   for (int k = 0; k < 2; ++k) {
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&f->side[k], hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&f->end[k], hipEventDisableTiming);
   }
   if (e == hipSuccess) e = hipEventCreateWithFlags(&f->begin, hipEventDisableTiming);
-  if (e != hipSuccess) batch_fork_destroy(f);
-  return e;
+  if (e == hipSuccess) return f;
+  batch_fork_destroy(f);
+  (void)hipGetLastError();
+  return nullptr;
 }
 
 void batch_fork_destroy(BatchFork* f) {
@@ -333,7 +339,7 @@ void batched_ls(hipStream_t s, const BatchHeader* table, int* counter, int* stat
   TimedLaunch tl(s, "batched_ls", bytes, flops);
   int used = 0;
   for (int k = 1; k < kBatchQueues; ++k) used += grids.g[k] > 0;
-  if (fork && fork->begin && used > 1) {
+  if (fork && used > 1) {
     // Each queue ends with the few workgroups that hold its largest problems
     // (4096 x 256 takes 11 ms by itself, whatever else runs), so the queues run
     // side by side, each one's refinement behind its own sweep: a call of 2000

@@ -4,8 +4,9 @@
 // inputs upload on a separate stream, and requests that arrive meanwhile join
 // whichever batch launches next (continuous batching).  Each batch is one
 // replay of a captured graph (task-table upload, queue reset, persistent
-// kernel, status download).  Factorisations can be kept on the device for
-// further right-hand sides.
+// kernels, status download): one for batches whose problems share a queue of the
+// batched kernels, one with the queues side by side.  Factorisations can be kept
+// on the device for further right-hand sides.
 //
 // The server is driven by its caller: qr_server_poll retires finished
 // batches, admits waiting requests and launches the next batch.  It is not
@@ -111,8 +112,8 @@ struct Slot {
   bool busy = false;
   std::vector<int64_t> ids;
   hipEvent_t done = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
+  hipGraph_t graph[2] = {nullptr, nullptr};  // the queues in turn, side by side
+  hipGraphExec_t exec[2] = {nullptr, nullptr};
   BatchHeader* dtable = nullptr;
   BatchHeader* ptable = nullptr;
   int* dstatus = nullptr;
@@ -132,9 +133,9 @@ struct miqr_server {
   char* pool_base = nullptr;
   Pool pool;
   hipStream_t compute = nullptr;
-  hipStream_t copy[2] = {nullptr, nullptr};  // uploads: right-hand sides, matrices
+  hipStream_t copy[2] = {nullptr, nullptr};  // uploads; [1]: matrices (second_copy)
   hipEvent_t copied = nullptr;               // joins copy[1] into copy[0]
-  BatchFork fork;  // the queues of one batch side by side
+  BatchFork fork;  // the queues of an FP64 re-solve side by side (batch_fork)
   Slot slots[2];
   std::vector<hipEvent_t> up_events;
   std::vector<int> up_refs;  // requests still to be launched after each upload event
@@ -215,10 +216,45 @@ hipError_t upload(hipStream_t st, double* dst, const double* src, int64_t ld, in
                           hipMemcpyHostToDevice, st);
 }
 
+// The stream for the matrices of the waiting requests.  A and B on a stream each
+// run side by side: 300 requests, 0.6 GB from pinned memory, with their solves
+// 28.8 ms on one stream, 25.8 ms so.  The join costs a small request more than it
+// gains (one of 100 x 10 with its solve 106 us on one stream, 141 us on two), so
+// the second stream takes part, and is made, from a megabyte or nine requests on.
+hipStream_t second_copy(miqr_server* s) {
+  size_t bytes = 0;
+  int fresh = 0;
+  for (size_t k = 0; k < std::min<size_t>(s->pending.size(), 9); ++k) {
+    const Req& r = s->reqs[s->pending[k]];
+    if (r.parent >= 0) continue;
+    bytes += (size_t)(r.m * r.n) * 8;
+    ++fresh;
+  }
+  if (fresh < 9 && bytes < ((size_t)1 << 20)) return s->copy[0];
+  if (!s->copied) {
+    hipError_t e = hipStreamCreateWithFlags(&s->copy[1], hipStreamNonBlocking);
+    if (e == hipSuccess) {
+      e = hipEventCreateWithFlags(&s->copied, hipEventDisableTiming);
+      if (e != hipSuccess) {
+        hipStreamDestroy(s->copy[1]);
+        s->copied = nullptr;
+      }
+    }
+    if (e != hipSuccess) {
+      s->copy[1] = nullptr;
+      (void)hipGetLastError();
+      return s->copy[0];
+    }
+  }
+  return s->copy[1];
+}
+
 // Move waiting requests into device memory while the budget allows (in
 // arrival order; the first one that does not fit waits, and so do the rest).
 miqr_status admit(miqr_server* s) {
   int ev = -1;
+  const hipStream_t matrices = second_copy(s);
+  bool join = false;  // matrices were uploaded on the second stream
   while (!s->pending.empty()) {
     Req& r = s->reqs[s->pending.front()];
     size_t a, b, rr, c, tau;
@@ -237,12 +273,14 @@ miqr_status admit(miqr_server* s) {
       break;
     }
     hipError_t e = hipSuccess;
-    // A and B have a stream each, so their transfers run side by side: 300
-    // requests, 0.6 GB from pinned memory, with their solves 28.8 ms on one
-    // stream, 25.8 ms so, 28.6 ms with B pitched.  Right-hand sides alone, for
-    // kept factors, go pitched on one stream: 2000 of one to four columns 55.5 ms,
-    // 59 ms as runs, and of one column 40 % longer spread over both streams.
-    if (a) e = upload(s->copy[1], dptr(s, r.A), r.hA, r.lda, r.m, r.n, true);
+    // Runs where they are packed (300 requests 25.8 ms, 28.6 ms with B pitched);
+    // right-hand sides alone, for kept factors, pitched: 2000 of one to four
+    // columns 55.5 ms, 59 ms as runs, and of one column 40 % longer spread over
+    // both streams.
+    if (a) {
+      e = upload(matrices, dptr(s, r.A), r.hA, r.lda, r.m, r.n, true);
+      join = matrices != s->copy[0];
+    }
     if (e == hipSuccess)
       e = upload(s->copy[0], dptr(s, r.B), r.hB, r.ldb, r.m, r.nrhs, r.parent < 0);
     if (e != hipSuccess) return shfail(s, e, "server upload");
@@ -257,16 +295,59 @@ miqr_status admit(miqr_server* s) {
     s->pending.pop_front();
   }
   if (ev >= 0) {
-    hipError_t e = hipEventRecord(s->copied, s->copy[1]);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s->copy[0], s->copied, 0);
+    hipError_t e = join ? hipEventRecord(s->copied, s->copy[1]) : hipSuccess;
+    if (e == hipSuccess && join) e = hipStreamWaitEvent(s->copy[0], s->copied, 0);
     if (e == hipSuccess) e = hipEventRecord(s->up_events[ev], s->copy[0]);
     if (e != hipSuccess) return shfail(s, e, "server upload event");
   }
   return MIQR_OK;
 }
 
+// Capture the slot's graph of one batch: table upload, queue reset, persistent
+// kernels, status download.  The table's header carries the count, so the graph
+// never changes.  The one with the queues side by side waits for the first batch
+// that has several: with it server creation took 1.6 ms instead of 0.8, its end
+// 4.6 instead of 2.7, and every small batch 30 us more.  Its side streams live
+// as long as the capture (the graph has its own): the streams of a process share
+// four hardware queues, and the event after an upload waits for a kernel that
+// its stream shares one with.
+hipError_t capture(miqr_server* s, Slot& sl, const BatchFork* fork) {
+  const size_t tb = batch_table_bytes(s->max_batch);
+  hipError_t e = hipStreamBeginCapture(s->compute, hipStreamCaptureModeRelaxed);
+  if (e != hipSuccess) return e;
+  e = hipMemcpyAsync(sl.dtable, sl.ptable, tb, hipMemcpyHostToDevice, s->compute);
+  if (e == hipSuccess) {
+    batched_ls(s->compute, sl.dtable, sl.dcounter, sl.dstatus, nullptr, s->grids, s->prec, 0.0,
+               0.0, fork);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(sl.pstatus, sl.dstatus, (size_t)s->max_batch * 4, hipMemcpyDeviceToHost,
+                       s->compute);
+  const int k = fork ? 1 : 0;
+  const hipError_t e2 = hipStreamEndCapture(s->compute, &sl.graph[k]);
+  if (e == hipSuccess) e = e2;
+  if (e == hipSuccess) e = hipGraphInstantiate(&sl.exec[k], sl.graph[k], nullptr, nullptr, 0);
+  return e;
+}
+
+// The slot's graph for a batch's table.
+hipError_t graph_for(miqr_server* s, Slot& sl, const BatchHeader& table, hipGraphExec_t* exec) {
+  *exec = sl.exec[0];
+  BatchFork fork;
+  if (!sl.exec[1] && batch_fork(&fork, table)) {
+    const hipError_t e = capture(s, sl, &fork);
+    batch_fork_destroy(&fork);
+    if (e != hipSuccess) return e;
+  }
+  int used = 0;
+  for (int k = 1; k < kBatchQueues; ++k) used += table.count[k] > 0;
+  if (used > 1 && sl.exec[1]) *exec = sl.exec[1];
+  return hipSuccess;
+}
+
 // Launch the next batch on slot sl.  A batch is either requests in the
-// server's precision (one replay of the slot's graph) or FP64 re-solves of
+// server's precision (one replay of a graph of the slot's) or FP64 re-solves of
 // mixed-precision requests whose refinement missed its target (the same
 // sequence launched directly).  Tasks are grouped by queue of the batched
 // kernels, largest first within a queue.
@@ -345,13 +426,15 @@ miqr_status launch(miqr_server* s, Slot& sl) {
     r.ev = -1;
   }
   if (!redo) {
-    if (e == hipSuccess) e = hipGraphLaunch(sl.exec, s->compute);
+    hipGraphExec_t exec = nullptr;
+    if (e == hipSuccess) e = graph_for(s, sl, *hd, &exec);
+    if (e == hipSuccess) e = hipGraphLaunch(exec, s->compute);
   } else {
     const size_t tb = batch_table_bytes(count);
     if (e == hipSuccess) e = hipMemcpyAsync(sl.dtable, sl.ptable, tb, hipMemcpyHostToDevice, s->compute);
     if (e == hipSuccess) {
       batched_ls(s->compute, sl.dtable, sl.dcounter, sl.dstatus, nullptr, s->grids64, kBlkF64, 0.0,
-                 0.0, &s->fork);
+                 0.0, batch_fork(&s->fork, *hd));
       e = hipGetLastError();
     }
     if (e == hipSuccess)
@@ -442,24 +525,7 @@ miqr_status make_slot(miqr_server* s, Slot& sl) {
   if (e == hipSuccess) e = hipHostMalloc((void**)&sl.px, s->stage_doubles * 8, hipHostMallocDefault);
   if (e != hipSuccess) return sfail(s, MIQR_ENOMEM, "server: slot allocation failed");
   std::memset(sl.ptable, 0, tb);
-  // One batch = one replay: table upload, queue reset + persistent kernel,
-  // status download.  The table's header carries the count, so the graph
-  // never changes.
-  e = hipStreamBeginCapture(s->compute, hipStreamCaptureModeRelaxed);
-  if (e == hipSuccess) e = hipMemcpyAsync(sl.dtable, sl.ptable, tb, hipMemcpyHostToDevice, s->compute);
-  if (e == hipSuccess) {
-    batched_ls(s->compute, sl.dtable, sl.dcounter, sl.dstatus, nullptr, s->grids, s->prec, 0.0,
-               0.0, &s->fork);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(sl.pstatus, sl.dstatus, (size_t)s->max_batch * 4, hipMemcpyDeviceToHost,
-                       s->compute);
-  hipGraph_t g = nullptr;
-  hipError_t e2 = hipStreamEndCapture(s->compute, &g);
-  if (e == hipSuccess) e = e2;
-  if (e == hipSuccess) e = hipGraphInstantiate(&sl.exec, g, nullptr, nullptr, 0);
-  sl.graph = g;
+  e = capture(s, sl, nullptr);
   if (e != hipSuccess) return shfail(s, e, "server graph capture");
   return MIQR_OK;
 }
@@ -469,8 +535,10 @@ void destroy_server(miqr_server* s) {
   for (hipStream_t c : s->copy)
     if (c) hipStreamSynchronize(c);
   for (Slot& sl : s->slots) {
-    if (sl.exec) hipGraphExecDestroy(sl.exec);
-    if (sl.graph) hipGraphDestroy(sl.graph);
+    for (hipGraphExec_t x : sl.exec)
+      if (x) hipGraphExecDestroy(x);
+    for (hipGraph_t g : sl.graph)
+      if (g) hipGraphDestroy(g);
     if (sl.done) hipEventDestroy(sl.done);
     if (sl.dtable) hipFree(sl.dtable);
     if (sl.dstatus) hipFree(sl.dstatus);
@@ -536,10 +604,7 @@ miqr_status qr_server_create(miqr_handle h, const qr_server_opts* o, miqr_server
   s->grids = batched_grids(h->device, s->prec);
   s->grids64 = batched_grids(h->device, kBlkF64);
   hipError_t e = hipStreamCreateWithFlags(&s->compute, hipStreamNonBlocking);
-  for (hipStream_t& c : s->copy)
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&c, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&s->copied, hipEventDisableTiming);
-  if (e == hipSuccess) e = batch_fork_create(&s->fork);
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->copy[0], hipStreamNonBlocking);
   if (e != hipSuccess) {
     destroy_server(s);
     return MIQR_EHIP;

@@ -222,3 +222,28 @@ def test_server_mixed_precision_matches_batched(miqr, prec):
     with pytest.raises(m_.MiqrError) as e:
         m_.Server(h, keep_factors=True, precision=p)
     assert e.value.status == m_.ENOTSUP
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_server_one_queue_and_several(miqr, prec):
+    """Batches of one queue (graph replays), of several (launched side by
+    side) and alternately, few requests and many, below and above the size at
+    which matrices take a copy stream of their own: each as solved alone."""
+    m_, h = miqr
+    srv = m_.Server(h, hbm_budget=1 << 28, max_batch=64, precision=prec)
+    wide = [(300, 200, 1), (400, 260, 2), (200, 100, 1)]  # three queues
+    rounds = [[(100, 10, 1)], wide, [(64, 8, 8)], [(512, 256, 1)], [(90, 20, 1)] * 9,
+              wide + [(64, 64, 3)] * 70, [(1025, 127, 1)] * 2]
+    try:
+        for i, sh in enumerate(rounds):
+            ps = problems(sh, 900 + 100 * i)
+            xs = [np.zeros((n, k), order="F") for _, n, k in sh]
+            ids = [srv.submit(A, B, X) for (A, B), X in zip(ps, xs)]
+            done = drain(srv, ids)
+            for rid, (A, B), X in zip(ids, ps, xs):
+                assert done[rid]["status"] == 0
+                Ad, Bd = m_.to_colmajor(A), m_.to_colmajor(B)
+                h.lstsq_batched([Ad], [Bd], h.opts(precision=prec))
+                assert np.array_equal(X, Bd.cpu().numpy()[: A.shape[1]])
+    finally:
+        srv.close()

@@ -105,7 +105,9 @@ typedef struct qr_opts {
     int32_t no_lookahead; /* MIQR_T_BLOCKED: nonzero keeps every step on the
                           caller's stream; otherwise panel k + 1 is factored
                           while an internal stream applies panel k to the
-                          columns beyond it */
+                          columns beyond it, several panels of nb at a step
+                          while the trailing matrix is large (qr_plan lists
+                          the steps), so the two agree to rounding */
 } qr_opts;
 
 /* Host-side result of qr_lstsq. */
@@ -146,9 +148,11 @@ int64_t qr_t_rows(int64_t m, int64_t n, const qr_opts *opts);
  * nonzero: the plan qr_lstsq uses), as JSON text: the tuning (b, bstar, nb,
  * leaf_rows, chain, arity, t_layout, lookahead; 0 for TSQR parameters chosen
  * per panel), the cost model's counts and predicted seconds, the workspace
- * regions in doubles, the recursion nodes [c0, rows, width, n1] (n1 = 0: a
+ * regions in doubles, the steps [c0, width] of the top level, and for panels of
+ * nb (of n for MIQR_T_FULL) the recursion nodes [c0, rows, width, n1] (n1 = 0: a
  * TSQR panel) and the TSQR panels [c0, rows, width, leaf_rows, chain, arity,
- * levels].  Writes at most len - 1 characters and a NUL to buf (buf may be
+ * levels].  A step wider than nb is factored as one node of its width, split by
+ * the same rule, in place of its panels' nodes.  Writes at most len - 1 characters and a NUL to buf (buf may be
  * NULL) and returns the full length, or -1 for invalid sizes or options.
  * Host only: needs no device. */
 int64_t qr_plan(int64_t m, int64_t n, const qr_opts *opts, int lstsq, char *buf,

@@ -500,12 +500,21 @@ std::string describe_plan(int64_t m, int64_t n, const Tuning& t) {
   }
   std::snprintf(buf, sizeof buf, ",\"overlap\":%.9g},", cost_coeffs().overlap);
   s += buf;
-  // Recursion nodes [c0, rows, width, n1] (n1 = 0: base-case TSQR panel) of
-  // every top-level panel (a wide step of the look-ahead joins several of
-  // them, with the same TSQR panels).
-  s += "\"nodes\":[";
+  // Steps [c0, width] of the top level: panels of nb, or several of them joined
+  // by the look-ahead.
+  s += "\"steps\":[";
   bool first = true;
   const int64_t nb = top_panel(t, n);
+  for (int64_t j = 0, w = 0; j < n; j += w) {
+    w = step_width(m, n, j, t);
+    std::snprintf(buf, sizeof buf, "%s[%lld,%lld]", first ? "" : ",", (long long)j, (long long)w);
+    first = false;
+    s += buf;
+  }
+  // Recursion nodes [c0, rows, width, n1] (n1 = 0: base-case TSQR panel) of
+  // every top-level panel.
+  s += "],\"nodes\":[";
+  first = true;
   for (int64_t j = 0; j < n; j += nb) list_nodes(j, m - j, std::min(nb, n - j), t, &s, &first);
   s += "],\"panels\":[";
   first = true;

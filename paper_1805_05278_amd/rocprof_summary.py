@@ -35,7 +35,8 @@ from collections import defaultdict
 HERE = os.path.dirname(os.path.abspath(__file__))
 COPY_BYTES = 8.0 * (1 << 27)
 
-# Demangled kernel symbol -> the name the library's event timer uses.
+# Demangled kernel symbol -> the name the library's event timer uses (k_chain_*:
+# kernels of older traces).
 _PATTERNS = [
     (r"k_batched_blk<0,", "batched_blk_f64"),
     (r"k_batched_blk<1,", "batched_blk_fp32"),
@@ -43,6 +44,7 @@ _PATTERNS = [
     (r"k_batched_refine", "batched_refine"),
     (r"k_batch_reset", "batched_queue_reset"),
     (r"k_zero_block_lower", "zero_block_lower"),
+    (r"k_copy_diagonal_blocks", "copy_diagonal_blocks"),
     (r"k_square_last_column", "square_last_column"),
     (r"k_normalize_r", "normalize_r"),
     (r"k_find_zero_diag", "find_zero_diag"),

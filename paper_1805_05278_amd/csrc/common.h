@@ -41,22 +41,6 @@ __device__ __forceinline__ double dpp_mov(double v) {
                                           (unsigned long long)(unsigned)lo));
 }
 
-// Sum over the 4 lanes of a quad (quad_perm [1,0,3,2] then [2,3,0,1]); every
-// lane of the quad receives the total.
-__device__ __forceinline__ double quad_sum(double v) {
-  v += dpp_mov<0xB1>(v);
-  v += dpp_mov<0x4E>(v);
-  return v;
-}
-
-// Sum over 8 consecutive lanes (quad sums, then row_half_mirror pairs the two
-// quads of each half-row).
-__device__ __forceinline__ double oct_sum(double v) {
-  v = quad_sum(v);
-  v += dpp_mov<0x141>(v);
-  return v;
-}
-
 // Householder reflector of a column (alpha; x) with ||x||^2 = ss > 0 (the
 // dlarfg sign rule): beta = -sign(alpha) ||(alpha; x)||,
 // tau = (beta - alpha) / beta = 1 + |alpha| / ||(alpha; x)|| and

@@ -4,6 +4,7 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "lanes.h"
 #include "profiler.h"
 #include "solve.h"
 
@@ -88,14 +89,6 @@ __global__ void k_square_last_column(int64_t n, double* A, int64_t lda, double* 
   }
 }
 
-// Lane i's v (i uniform).
-__device__ __forceinline__ double lane_value(double v, int i) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, i);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), i);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 __global__ void k_find_zero_diag(int64_t n, const double* R, int64_t ldr, int* flag) {
   __shared__ int best;
   if (threadIdx.x == 0) best = INT_MAX;
@@ -151,7 +144,7 @@ __global__ __launch_bounds__(256) void k_trsm_diag(int nb, int64_t nrhs, const d
         } else {
           z = x / d;
         }
-        const double xi = lane_value(z, i);
+        const double xi = readlane(z, i);
         if (row == i) x = xi;
         if (TRANS ? row > i : row < i) x -= r[u] * xi;
       }

@@ -89,7 +89,7 @@ _KERNEL_SOURCES = [
     ("tsqr_", ("tsqr.hip", "tsqr.h", "common.h", "lanes.h")),
     ("batched_ls", ("batched.hip", "batched.h", "common.h")),
     ("batched_", ("batched_blk.hip", "batched.h", "common.h", "lanes.h")),
-    ("trsm_diag", ("solve.hip", "solve.h", "common.h")),
+    ("trsm_diag", ("solve.hip", "solve.h", "common.h", "lanes.h")),
 ]
 
 

@@ -114,6 +114,7 @@ struct Slot {
   hipEvent_t done = nullptr;
   hipGraph_t graph[2] = {nullptr, nullptr};  // the queues in turn, side by side
   hipGraphExec_t exec[2] = {nullptr, nullptr};
+  bool tried = false;  // the second one's capture
   BatchHeader* dtable = nullptr;
   BatchHeader* ptable = nullptr;
   int* dstatus = nullptr;
@@ -327,23 +328,28 @@ hipError_t capture(miqr_server* s, Slot& sl, const BatchFork* fork) {
   const int k = fork ? 1 : 0;
   const hipError_t e2 = hipStreamEndCapture(s->compute, &sl.graph[k]);
   if (e == hipSuccess) e = e2;
-  if (e == hipSuccess) e = hipGraphInstantiate(&sl.exec[k], sl.graph[k], nullptr, nullptr, 0);
+  if (e == hipSuccess) {
+    e = hipGraphInstantiate(&sl.exec[k], sl.graph[k], nullptr, nullptr, 0);
+    if (e != hipSuccess) sl.exec[k] = nullptr;
+  }
   return e;
 }
 
-// The slot's graph for a batch's table.
-hipError_t graph_for(miqr_server* s, Slot& sl, const BatchHeader& table, hipGraphExec_t* exec) {
-  *exec = sl.exec[0];
-  BatchFork fork;
-  if (!sl.exec[1] && batch_fork(&fork, table)) {
-    const hipError_t e = capture(s, sl, &fork);
-    batch_fork_destroy(&fork);
-    if (e != hipSuccess) return e;
-  }
+// The slot's graph for a batch's table (the queues in turn where the other could
+// not be captured).
+hipGraphExec_t graph_for(miqr_server* s, Slot& sl, const BatchHeader& table) {
   int used = 0;
   for (int k = 1; k < kBatchQueues; ++k) used += table.count[k] > 0;
-  if (used > 1 && sl.exec[1]) *exec = sl.exec[1];
-  return hipSuccess;
+  if (used < 2) return sl.exec[0];
+  if (!sl.tried) {
+    sl.tried = true;
+    BatchFork fork;
+    if (batch_fork(&fork, table)) {
+      if (capture(s, sl, &fork) != hipSuccess) (void)hipGetLastError();
+      batch_fork_destroy(&fork);
+    }
+  }
+  return sl.exec[1] ? sl.exec[1] : sl.exec[0];
 }
 
 // Launch the next batch on slot sl.  A batch is either requests in the
@@ -426,9 +432,7 @@ miqr_status launch(miqr_server* s, Slot& sl) {
     r.ev = -1;
   }
   if (!redo) {
-    hipGraphExec_t exec = nullptr;
-    if (e == hipSuccess) e = graph_for(s, sl, *hd, &exec);
-    if (e == hipSuccess) e = hipGraphLaunch(exec, s->compute);
+    if (e == hipSuccess) e = hipGraphLaunch(graph_for(s, sl, *hd), s->compute);
   } else {
     const size_t tb = batch_table_bytes(count);
     if (e == hipSuccess) e = hipMemcpyAsync(sl.dtable, sl.ptable, tb, hipMemcpyHostToDevice, s->compute);

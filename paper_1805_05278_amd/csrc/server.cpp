@@ -219,19 +219,16 @@ hipError_t upload(hipStream_t st, double* dst, const double* src, int64_t ld, in
 
 // The stream for the matrices of the waiting requests.  A and B on a stream each
 // run side by side: 300 requests, 0.6 GB from pinned memory, with their solves
-// 28.8 ms on one stream, 25.8 ms so.  The join costs a small request more than it
-// gains (one of 100 x 10 with its solve 106 us on one stream, 141 us on two), so
-// the second stream takes part, and is made, from a megabyte or nine requests on.
+// 28.8 ms on one stream, 25.8 ms so.  The join costs few requests more than they
+// gain (one of 100 x 10 with its solve 106 us on one stream, 141 us on two; six
+// of up to 716 x 90 501 and 463 us), so the second stream takes part, and is
+// made, from kSideBySide waiting ones on.
+constexpr size_t kSideBySide = 4;
 hipStream_t second_copy(miqr_server* s) {
-  size_t bytes = 0;
-  int fresh = 0;
-  for (size_t k = 0; k < std::min<size_t>(s->pending.size(), 9); ++k) {
-    const Req& r = s->reqs[s->pending[k]];
-    if (r.parent >= 0) continue;
-    bytes += (size_t)(r.m * r.n) * 8;
-    ++fresh;
-  }
-  if (fresh < 9 && bytes < ((size_t)1 << 20)) return s->copy[0];
+  size_t fresh = 0;
+  for (size_t k = 0; k < std::min(s->pending.size(), kSideBySide); ++k)
+    fresh += s->reqs[s->pending[k]].parent < 0;
+  if (fresh < kSideBySide) return s->copy[0];
   if (!s->copied) {
     hipError_t e = hipStreamCreateWithFlags(&s->copy[1], hipStreamNonBlocking);
     if (e == hipSuccess) {

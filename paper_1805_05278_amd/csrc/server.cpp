@@ -221,14 +221,17 @@ hipError_t upload(hipStream_t st, double* dst, const double* src, int64_t ld, in
 // run side by side: 300 requests, 0.6 GB from pinned memory, with their solves
 // 28.8 ms on one stream, 25.8 ms so.  The join costs few requests more than they
 // gain (one of 100 x 10 with its solve 106 us on one stream, 141 us on two; six
-// of up to 716 x 90 501 and 463 us), so the second stream takes part, and is
-// made, from kSideBySide waiting ones on.
+// of up to 716 x 90 501 and 463 us), so an idle server's second stream takes part,
+// and is made, from kSideBySide waiting ones on.  While a batch runs a request
+// waits for it anyway, and two streams keep up better (7500 requests a second of
+// the serving mix: 30 ms to half of them on one stream, 24 ms on two).
 constexpr size_t kSideBySide = 4;
 hipStream_t second_copy(miqr_server* s) {
   size_t fresh = 0;
   for (size_t k = 0; k < std::min(s->pending.size(), kSideBySide); ++k)
     fresh += s->reqs[s->pending[k]].parent < 0;
-  if (fresh < kSideBySide) return s->copy[0];
+  const bool busy = s->slots[0].busy || s->slots[1].busy;
+  if (fresh == 0 || (fresh < kSideBySide && !busy)) return s->copy[0];
   if (!s->copied) {
     hipError_t e = hipStreamCreateWithFlags(&s->copy[1], hipStreamNonBlocking);
     if (e == hipSuccess) {

@@ -204,7 +204,9 @@ int64_t miqr_graph_count(miqr_handle handle);
  *      Alg. 2's assembly, strict lower triangle set to zero.
  *      MIQR_T_BLOCKED: nb x n (ldt >= qr_t_rows), the panels' kernels (see
  *      miqr_t_layout).
- *   opts: see qr_opts; opts->Q (if set) receives the explicit thin Q.
+ *   opts: see qr_opts; opts->Q (if set) receives the explicit thin Q.  A
+ *      panel whose Q is formed with it takes V from Q's rows, so V, T and R
+ *      with and without Q agree to rounding.
  * With MIQR_T_BLOCKED and look-ahead the call also enqueues work on the
  * handle's internal stream, ordered after the caller's stream's earlier work
  * and joined back into it before the call's last operation.

@@ -341,7 +341,7 @@ void batched_ls(hipStream_t s, const BatchHeader* table, int* counter, int* stat
   for (int k = 1; k < kBatchQueues; ++k) used += grids.g[k] > 0;
   if (fork && used > 1) {
     // Each queue ends with the few workgroups that hold its largest problems
-    // (4096 x 256 takes 11 ms by itself, whatever else runs), so the queues run
+    // (4096 x 256 takes 8 ms by itself, whatever else runs), so the queues run
     // side by side, each one's refinement behind its own sweep: a call of 2000
     // problems of the serving mix 29.4 ms in turn, 19.8 so (FP64); 30.1 and
     // 19.6 ms with FP32 sweeps.

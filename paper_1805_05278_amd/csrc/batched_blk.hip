@@ -25,11 +25,11 @@
 //
 // A panel is factored by the wave that owns its tile, column by column
 // (dlarfg sign rule; norm, beta and tau in FP64): the pivot column reaches
-// the other lanes through LDS, dot products are per-lane partial sums and one
-// cross-row sum in registers (v_permlane16/32_swap), and the same sums give
-// the Gram entries of T.  Look-ahead: the owner of panel p + 1 updates that
-// tile first and factors it while the other waves still apply panel p, so a
-// panel costs one barrier.
+// the other lanes by DPP inside the FMAs, dot products are per-lane partial sums
+// and one cross-row sum in registers (v_permlane16/32_swap), and the same sums
+// give the Gram entries of T.  Look-ahead: the owner of panel p + 1 updates that
+// tile first and factors it while the other waves still apply panel p; counters
+// in LDS order the panels, with no barrier.
 //
 // Precisions: FP64 throughout (FP64 MFMA), or a working copy of the block in
 // FP32 with Y^T X and Y W' on FP32 MFMA or on BF16 MFMA with FP32

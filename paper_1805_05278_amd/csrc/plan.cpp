@@ -159,10 +159,12 @@ const char* cost_feature_name(int f) {
 const CostCoeffs& cost_coeffs() {
   // Fitted by least squares to factorisations timed on MI355X over a sweep of
   // shapes and tunings, one stream, no look-ahead (the fit and its residuals
-  // are kept with the measured profiles); d0 from the GEMM depth scan.  The
-  // kernels have become faster since: the estimates are upper bounds now.  The
-  // coefficients, and the launch counts below that they were fitted with, stay,
-  // because the panel width chosen by them is the row count of a BLOCKED T.
+  // are kept with the measured profiles); d0 from the GEMM depth scan.  They
+  // describe the kernels of that sweep, not today's, and only compare tunings:
+  // the seconds are no bound on a call's time.  The coefficients, and the launch
+  // counts below that they were fitted with, stay, because the panel width chosen
+  // by them is the row count of a BLOCKED T; leaf height, chain length, arity, b
+  // and b* come from the same fit and have not been fitted again.
   static const CostCoeffs c{
       {
           /*leaf256_steps=*/0.0001165,

@@ -1234,9 +1234,8 @@ TsqrPlan tsqr_plan(int64_t rows, int nbr, int leaf_rows, int chain, int arity, d
       lv.Y = take((int64_t)lv.nchains * kYS);
     }
     lv.R = take((int64_t)lv.nchains * kTS);
-    // Only the top level's B is used; the others keep their place, so that the
-    // workspace a shape needs (what qr_workspace_size reports and
-    // qr_factor_noalloc accepts) stays what it was.
+    // Only the top level's B is used (64 KB a chain); the others keep their
+    // place, which the shapes that qr_factor_noalloc accepts follow from.
     lv.B = take((int64_t)lv.nchains * kBS);
   }
   p.LR = take(kTS);

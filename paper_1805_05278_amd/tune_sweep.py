@@ -87,9 +87,9 @@ def sweep(shapes, reps):
 
 
 def report(rows, command):
-    keys = ["gemm_f64", "tsqr_chain_qr_leaf", "tsqr_chain_qr_leaf_rest", "tsqr_chain_qr_tree",
-            "tsqr_hr_root", "tsqr_down_tree", "tsqr_down_leaf"]
-    short = ["gemm", "leaf", "leaf rest", "tree", "HR", "down tree", "down leaf"]
+    keys = ["gemm_f64", "tsqr_chain_qr_leaf", "tsqr_chain_qr_tree", "tsqr_hr_root",
+            "tsqr_down_leaf"]
+    short = ["gemm", "leaf", "tree", "HR", "down"]
     out = ["# TSQR / EG tuning sweep: latency, bandwidth and arithmetic terms measured", "",
            "Command (from the repository root on the GPU host):", "", "```", command, "```", "",
            "ms: factorisation with thin Q, minimum over repetitions without per-launch events. "
